@@ -744,6 +744,14 @@ int compile_source(const std::string &src, const std::string &arch, std::vector<
     return SSA_OK;
 }
 
+// A kernel is named by its source. Forming and hashing that text takes longer than
+// a small run, so its hash and length are kept by what it is generated from
+// (kernel_structure); the text itself is formed only to compile it.
+struct SourceId {
+    uint64_t hash = 0;
+    size_t size = 0;
+};
+
 struct Loaded {
     hipModule_t mod = nullptr;
     hipFunction_t kernel = nullptr;
@@ -755,19 +763,50 @@ struct Loaded {
     // that it holds more than half of a CU's LDS: one workgroup, i.e. one
     // event-loop wave per SIMD, per CU, whatever the dispatcher would pack
     unsigned pc_lds_pad = 0;
+    int cus = 0;
+    int per_cu[5] = {};   // resident workgroups per CU of 64, 128, 192 and 256 threads, and of ssa_kernel_pc
+    int resident(int block) const { return per_cu[block == 512 ? 4 : block / 64 - 1]; }
 };
 
 std::mutex g_jit_mu;
 std::unordered_map<std::string, Loaded> g_loaded;  // key: device + source hash
 
-// load_if_missing = false: only a kernel an earlier run loaded on this
-// device (no compilation, no module load: they allocate)
-int get_kernel(const std::string &src, Loaded &out, bool load_if_missing = true)
+int build_source(const ssa_run_desc *d, std::string &src);
+std::string kernel_structure(const ssa_run_desc *d);
+
+std::mutex g_ids_mu;
+std::unordered_map<std::string, SourceId> g_ids;   // by kernel_structure
+constexpr size_t kMaxIds = 4096;                   // (emptied when full: an id is formed again)
+
+SourceId source_id(const ssa_run_desc *d)
+{
+    const std::string key = kernel_structure(d);
+    {
+        std::lock_guard<std::mutex> lk(g_ids_mu);
+        auto it = g_ids.find(key);
+        if (it != g_ids.end())
+            return it->second;
+    }
+    std::string src;
+    build_source(d, src);
+    SourceId id;
+    id.hash = fnv1a(src);
+    id.size = src.size();
+    std::lock_guard<std::mutex> lk(g_ids_mu);
+    if (g_ids.size() >= kMaxIds)
+        g_ids.clear();
+    g_ids[key] = id;
+    return id;
+}
+
+// The kernel of a descriptor whose source has that id. load_if_missing = false: only
+// a kernel an earlier run loaded on this device (no compilation, no module load: they
+// allocate)
+int get_kernel(const ssa_run_desc *d, const SourceId &id, Loaded &out, bool load_if_missing = true)
 {
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
-    const std::string key = std::to_string(dev) + ":" + std::to_string(fnv1a(src)) + ":" +
-                            std::to_string(src.size());
+    const std::string key = std::to_string(dev) + ":" + std::to_string(id.hash) + ":" + std::to_string(id.size);
     std::lock_guard<std::mutex> lk(g_jit_mu);
     auto it = g_loaded.find(key);
     if (it != g_loaded.end()) {
@@ -778,6 +817,8 @@ int get_kernel(const std::string &src, Loaded &out, bool load_if_missing = true)
         return fail(SSA_E_INVALID, "ssa_ensemble_run_noalloc: the kernel for these networks and this precision is "
                                    "not loaded on this device; run ssa_ensemble_run (or ssa_autotune) with them "
                                    "once first");
+    std::string src;
+    build_source(d, src);
     std::vector<char> code;
     int rc = compile_source(src, "gfx950", code);
     if (rc != SSA_OK)
@@ -804,6 +845,10 @@ int get_kernel(const std::string &src, Loaded &out, bool load_if_missing = true)
         if (want > lds_static && want <= lds_block)
             ld.pc_lds_pad = (unsigned)(want - lds_static);
     }
+    HIP_TRY(hipDeviceGetAttribute(&ld.cus, hipDeviceAttributeMultiprocessorCount, dev));
+    for (int i = 0; i < 4; ++i)
+        HIP_TRY(hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&ld.per_cu[i], ld.kernel, 64 * (i + 1), 0));
+    HIP_TRY(hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&ld.per_cu[4], ld.kernel_pc, 512, ld.pc_lds_pad));
     g_loaded[key] = ld;
     out = ld;
     return SSA_OK;
@@ -821,10 +866,10 @@ std::mutex g_tune_mu;
 std::unordered_map<std::string, Tuned> g_tuned;
 bool g_tune_loaded = false;
 
-std::string tune_key(const ssa_run_desc *d, const std::string &src)
+std::string tune_key(const ssa_run_desc *d, const SourceId &id)
 {
     std::ostringstream k;
-    k << std::hex << fnv1a(src) << std::dec << ":" << d->n_snap << ":" << d->t_end << ":" << d->max_events;
+    k << std::hex << id.hash << std::dec << ":" << d->n_snap << ":" << d->t_end << ":" << d->max_events;
     for (int i = 0; i < d->n_items; ++i)
         k << ":" << d->items[i].n_traj;
     return k.str();
@@ -1027,6 +1072,34 @@ int validate_desc(const ssa_run_desc *d)
     return SSA_OK;
 }
 
+// Everything that the kernel source of a descriptor is generated from, as bytes: mode,
+// and per item the network, whether its rates are per lane, and its recorded reactions.
+std::string kernel_structure(const ssa_run_desc *d)
+{
+    std::string k;
+    k.reserve(1024);
+    auto put = [&k](const void *p, size_t n) { k.append((const char *)p, n); };
+    auto num = [&put](int64_t v) { put(&v, sizeof v); };
+    for (int32_t v : {d->format, d->accum, d->rounding, d->norm, d->n_items})
+        num(v);
+    for (int i = 0; i < d->n_items; ++i) {
+        const ssa_item &it = d->items[i];
+        const Model &md = it.model->m;
+        num(md.N);
+        num(md.M);
+        put(md.order.data(), md.order.size() * sizeof(int32_t));
+        put(md.nu.data(), md.nu.size() * sizeof(int32_t));
+        for (const ssa_law &l : md.law) {   // (constants are run-time data)
+            num(l.kind);
+            num(l.kind == SSA_LAW_MASS_ACTION ? 0 : l.regulator);
+            num(l.kind == SSA_LAW_MASS_ACTION ? 0 : l.h);
+        }
+        num(it.set_rates != nullptr && it.n_sets > 1);
+        num((int64_t)(it.record_cap > 0 ? it.record_mask : 0ull));
+    }
+    return k;
+}
+
 // Kernel source and flags for a descriptor (no device needed).
 int build_source(const ssa_run_desc *d, std::string &src)
 {
@@ -1186,6 +1259,46 @@ int dalloc(ssa_run *r, T **p, size_t n)
     return SSA_OK;
 }
 
+// Timing events of finished runs, kept per device for later ones (at most kMaxEvents).
+constexpr size_t kMaxEvents = 256;
+struct EventPool {
+    std::mutex mu;
+    std::vector<hipEvent_t> free;
+};
+EventPool g_events[kMaxDevices];
+
+int event_take(int dev, hipEvent_t *e)
+{
+    *e = nullptr;
+    if (dev >= 0 && dev < kMaxDevices) {
+        EventPool &p = g_events[dev];
+        std::lock_guard<std::mutex> lk(p.mu);
+        if (!p.free.empty()) {
+            *e = p.free.back();
+            p.free.pop_back();
+            return SSA_OK;
+        }
+    }
+    HIP_TRY(hipEventCreate(e));
+    return SSA_OK;
+}
+
+// reusable: the event has completed, or was never recorded
+void event_give(int dev, hipEvent_t e, bool reusable)
+{
+    if (!e)
+        return;
+    if (reusable && dev >= 0 && dev < kMaxDevices) {
+        EventPool &p = g_events[dev];
+        std::lock_guard<std::mutex> lk(p.mu);
+        if (p.free.size() < kMaxEvents) {
+            p.free.push_back(e);
+            return;
+        }
+    }
+    (void)hipEventDestroy(e);
+}
+
 // Snapshot rows [k_lo, k_hi) of chunk c: with first_window w > 0 the first
 // chunk holds rows [0, w) and the others split [w, K) evenly; else all split
 // [0, K) evenly.
@@ -1310,10 +1423,17 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
     HIP_TRY(hipGetDevice(&r->device));
     r->stream = (hipStream_t)d->hip_stream;
     r->K = d->n_snap;
-    std::string src;
-    build_source(d, src);
+    if (!r->noalloc) {
+        // the tables' host copy lives until this call returns: a captured copy of it
+        // would be replayed from freed memory
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        HIP_TRY(hipStreamIsCapturing(r->stream, &cap));
+        if (cap != hipStreamCaptureStatusNone)
+            return fail(SSA_E_DEVICE, "ssa_ensemble_run cannot be captured into a graph: its stream is capturing");
+    }
+    const SourceId id = source_id(d);
     Loaded ld;
-    int rc = get_kernel(src, ld, !r->noalloc);
+    int rc = get_kernel(d, id, ld, !r->noalloc);
     if (rc != SSA_OK)
         return rc;
     r->vgprs = ld.vgprs;
@@ -1321,7 +1441,7 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
     // launch shape chosen by ssa_autotune for this kernel and workload, if any
     Tuned tuned;
     const bool have_tuned = (d->block_size == 0 || d->grid_size == 0 || d->n_chunks == 0 || d->placement == 0) &&
-                            tune_lookup(tune_key(d, src), tuned);
+                            tune_lookup(tune_key(d, id), tuned);
     const bool wide = d->format == SSA_FMT_FP64;
     int n_chunks = d->n_chunks == 0 ? (have_tuned ? tuned.chunks : 1) : d->n_chunks;
     int window = d->n_chunks == 0 ? (have_tuned ? tuned.window : 0) : d->first_window;
@@ -1441,12 +1561,10 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
         char *base = nullptr;
         if ((rc = dalloc(r, &base, blob.size())))
             return rc;
-        if (!blob.empty()) {
-            if (r->noalloc)   // ordered on the run's stream after earlier work there
-                HIP_TRY(hipMemcpyAsync(base, blob.data(), blob.size(), hipMemcpyHostToDevice, r->stream));
-            else
-                HIP_TRY(hipMemcpy(base, blob.data(), blob.size(), hipMemcpyHostToDevice));
-        }
+        // ordered on the run's stream, after earlier work there (from pageable memory, the
+        // call returns once the bytes have been taken)
+        if (!blob.empty())
+            HIP_TRY(hipMemcpyAsync(base, blob.data(), blob.size(), hipMemcpyHostToDevice, r->stream));
         r->t64 = (double *)(base + off_t64);
         r->t32 = (float *)(base + off_t32);
         for (int i = 0; i < d->n_items; ++i) {
@@ -1457,14 +1575,11 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
     }
 
     // launch shape: enough waves to cover the ensemble, at most what stays resident
-    int cus = 0;
-    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, r->device));
+    const int cus = ld.cus;
     r->block = d->block_size ? d->block_size : (have_tuned ? tuned.block : 256);
     if (r->block == 512)
         r->vgprs = ld.vgprs_pc;
-    int per_cu = 0;
-    HIP_TRY(hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, r->block == 512 ? ld.kernel_pc : ld.kernel,
-                                                              r->block, r->block == 512 ? ld.pc_lds_pad : 0u));
+    const int per_cu = ld.resident(r->block);
     // a workgroup that cannot be resident at all (registers or LDS beyond a
     // CU's) would fail at dispatch: refuse it here
     if (per_cu < 1)
@@ -1498,15 +1613,16 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
         r->queued = true;
         return dispatch_launch(r, d, ld, n_chunks);
     }
-    HIP_TRY(hipEventCreate(&r->ev0));
-    HIP_TRY(hipEventCreate(&r->ev1));
+    if ((rc = event_take(r->device, &r->ev0)) || (rc = event_take(r->device, &r->ev1)))
+        return rc;
     // A captured graph pays off only over long chunk sequences: capture and
     // instantiation cost more than a few direct launches.
     r->graph = n_chunks > kGraphMinChunks;
     if (!r->graph) {
         r->kev.resize(2 * n_chunks);
         for (auto &e : r->kev)
-            HIP_TRY(hipEventCreate(&e));
+            if ((rc = event_take(r->device, &e)))
+                return rc;
     }
     HIP_TRY(hipEventRecord(r->ev0, r->stream));
     r->queued = true;
@@ -1553,13 +1669,11 @@ void release(ssa_run *r)
         (void)hipGraphDestroy(r->g);
     if (r->cap)
         (void)hipStreamDestroy(r->cap);
+    // events of a run that ended in order have completed (ev1 comes last on the stream)
     for (auto e : r->kev)
-        if (e)
-            (void)hipEventDestroy(e);
-    if (r->ev0)
-        (void)hipEventDestroy(r->ev0);
-    if (r->ev1)
-        (void)hipEventDestroy(r->ev1);
+        event_give(r->device, e, r->ev1_recorded);
+    event_give(r->device, r->ev0, r->ev1_recorded);
+    event_give(r->device, r->ev1, r->ev1_recorded);
     for (auto &o : r->owned)
         cache_give(r->device, o.first, o.second);
     delete r;
@@ -1830,14 +1944,11 @@ int ssa_autotune(const ssa_run_desc *desc, ssa_tune_result *res)
     int rc = validate_desc(desc);
     if (rc != SSA_OK)
         return rc;
-    std::string src;
-    build_source(desc, src);
+    const SourceId id = source_id(desc);
     Loaded ld;
-    if ((rc = get_kernel(src, ld)) != SSA_OK)
+    if ((rc = get_kernel(desc, id, ld)) != SSA_OK)
         return rc;
-    int dev = 0, cus = 0;
-    HIP_TRY(hipGetDevice(&dev));
-    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const int cus = ld.cus;
     int64_t total = 0;
     for (int i = 0; i < desc->n_items; ++i)
         total += desc->items[i].n_traj;
@@ -1866,9 +1977,7 @@ int ssa_autotune(const ssa_run_desc *desc, ssa_tune_result *res)
         }
     }
     for (int block : {64, 256}) {
-        int per_cu = 0;
-        HIP_TRY(hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ld.kernel, block, 0));
-        per_cu = std::max(per_cu, 1);
+        const int per_cu = std::max(ld.resident(block), 1);
         const int64_t need = std::max<int64_t>(1, (total + block - 1) / block);
         const int64_t resident = (int64_t)per_cu * cus;
         const int waves_per_block = block / 64;
@@ -1888,9 +1997,7 @@ int ssa_autotune(const ssa_run_desc *desc, ssa_tune_result *res)
     // 512-thread workgroups: one event-loop wave per SIMD, each paired with
     // the wave that forms its draws
     {
-        int per_cu = 0;
-        HIP_TRY(hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ld.kernel_pc, 512, ld.pc_lds_pad));
-        if (per_cu >= 1) {
+        if (ld.resident(512) >= 1) {
             const int64_t need = std::max<int64_t>(1, (total + 255) / 256);
             const int64_t g = std::min<int64_t>(need, cus);
             // producers on their own or the next SIMD; claims as they come, or
@@ -1969,7 +2076,7 @@ int ssa_autotune(const ssa_run_desc *desc, ssa_tune_result *res)
             best.ms = ms;
         }
     }
-    tune_store(tune_key(desc, src), best);
+    tune_store(tune_key(desc, id), best);
     if (res) {
         res->block_size = best.block;
         res->grid_size = best.grid;
