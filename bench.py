@@ -54,7 +54,7 @@ def parse():
     p.add_argument("--grid", type=int, default=0)
     p.add_argument("--first-window", type=int, default=0)
     p.add_argument("--placement", type=int, default=0,
-                   help="0: autotuned; else 1 | 2 (producer on the next SIMD) | 4 (wave-major first claims)")
+                   help="0: autotuned; else 1 | 4 (wave-major first claims, up to 256 threads)")
     return p.parse_args()
 
 
@@ -191,6 +191,15 @@ def measured_traffic(workload, mode, kernel_file):
     return None
 
 
+def kernel_name(info):
+    """The kernel of a launch: 512-thread workgroups are pipelined, one or two to a CU."""
+    import torch
+    if info["block_size"] != 512:
+        return "ssa_kernel"
+    cus = torch.cuda.get_device_properties(torch.cuda.current_device()).multi_processor_count
+    return "ssa_kernel_ph" if info["grid_size"] > cus else "ssa_kernel_pl"
+
+
 def physical_cores():
     """Distinct (package, core) pairs among the CPUs this process may run on."""
     try:
@@ -268,9 +277,9 @@ def main():
         fidelity["ks_fail"] = fails
 
     # roofline: VALU slots of one event on the every-event path of the launched
-    # code object, counted on its one-wave event loop (ssa_kernel). With producer
-    # waves (ssa_kernel_pc, 512-thread workgroups) the same per-event work is
-    # split between the paired waves; the LDS ring traffic is not counted.
+    # code object, counted on its one-wave event loop (ssa_kernel). In the pipelined
+    # kernels (ssa_kernel_pl, ssa_kernel_ph: 512-thread workgroups) the same per-event
+    # work is split between a workgroup's waves; the LDS traffic is not counted.
     # Several networks in one launch: the object's lightest loop would understate
     # the work, so each network's slots are counted on its own single-network
     # object and weighted by the events that network fired.
@@ -332,7 +341,7 @@ def main():
         "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_VALU_SLOTS / 1e12,
                      "unit": "TVALU-slot/s", "frac": achieved / PEAK_VALU_SLOTS,
                      "traffic": measured_traffic(W.name, args.mode, ve["file"]),
-                     "kernel": "ssa_kernel_pc" if main_res["info"]["block_size"] == 512 else "ssa_kernel",
+                     "kernel": kernel_name(main_res["info"]),
                      "kernel_object": os.path.basename(ve["file"]), "kernel_ms": ms,
                      "valu_slots_per_event": ve["valu_slots"], "valu_insts_per_event": ve["valu_insts"]},
     }
@@ -346,7 +355,7 @@ def main():
     if not passed:
         out["value_failing_fidelity"] = rate
     out["fp64"]["kernel_object"] = os.path.basename(ve_ref["file"])
-    out["fp64"]["kernel"] = "ssa_kernel_pc" if ref_res["info"]["block_size"] == 512 else "ssa_kernel"
+    out["fp64"]["kernel"] = kernel_name(ref_res["info"])
     if args.valu_peak:
         out["valu_peak"] = valu_peak(log)
     if args.copy_calib:

@@ -167,12 +167,16 @@ typedef struct ssa_item {
  *     launch. 0 = the autotuned choice for this kernel and workload shape if
  *     ssa_autotune stored one, else 1.
  *   block_size, grid_size: launch shape; 0 = the autotuned choice if stored,
- *     else 256 threads and enough workgroups for one trajectory per lane (up
- *     to what stays resident). block_size a multiple of 64 up to 256, or 512:
- *     then waves 0-3 of each workgroup run trajectories and wave w + 4, on
- *     the same SIMD as wave w, forms wave w's random draws ahead of use and
- *     passes them through LDS (results are bit-identical: the draws are the
- *     same function of seed, trajectory and event index).
+ *     else 512 threads and workgroups for one trajectory per lane (up to what
+ *     stays resident). block_size a multiple of 64 up to 256: every wave runs 64
+ *     trajectories. 512: the pipelined kernel, where the eight waves of a workgroup
+ *     run the events of 64 trajectories together (draws, events, clock and rows in
+ *     waves of their own, passing batches through LDS); a grid_size counts 256
+ *     trajectories a workgroup there too, so four workgroups are launched for each
+ *     (up to two per CU). A network whose batches do not fit a CU's LDS runs on
+ *     256 threads. Results are bit-identical in every shape: the draws are the
+ *     same function of seed, trajectory and event index. ssa_run_info reports
+ *     the shape launched.
  *   reorder: chunked runs only. 0 or 1: before each chunk after the first,
  *     trajectories are claimed in order of the events they fired in the
  *     previous chunk, heaviest first (results are unchanged: draws are keyed
@@ -187,42 +191,25 @@ typedef struct ssa_item {
  *   placement: SSA_PLACE_AUTO, or SSA_PLACE_EXPLICIT | SSA_PLACE_* flags
  *     (else SSA_E_INVALID). Results do not depend on it: draws are keyed by
  *     trajectory id, not by lane. */
-/* Placement of work in a launch (ssa_run_desc.placement). */
+/* Placement of work in a launch (ssa_run_desc.placement). The flags that place the
+ * draw-forming waves of 512-thread workgroups are accepted and reported and have no
+ * effect: the pipelined kernel divides a workgroup's work one way. */
 #define SSA_PLACE_AUTO 0               /* the autotuned choice if stored, else none of the flags */
 #define SSA_PLACE_EXPLICIT 1           /* the flags below are the caller's choice            */
-#define SSA_PLACE_NEIGHBOUR_PRODUCER 2 /* 512-thread workgroups: event-loop wave c takes its
-                                          draws from the producer on the next SIMD (mod 4),
-                                          so a wave left running alone has its SIMD to itself */
-#define SSA_PLACE_WAVE_MAJOR 4         /* single-item runs: each launch's first claims are
-                                          static, wave-major (the first 64 claims of the
-                                          claim order go to wave 0 of workgroup 0, the next
-                                          to wave 0 of workgroup 1, ...), so after a
-                                          reordering window the heaviest trajectories share
-                                          one wave per workgroup                            */
-#define SSA_PLACE_SOLO_WAVE0 8         /* 512-thread workgroups, one-item launches (SSA_E_INVALID
-                                          otherwise): event-loop wave 0 runs with its
-                                          SIMD to itself (producers feed the next SIMD's wave,
-                                          event-loop wave 3 forms its own draws, wave 4 does
-                                          not run); with SSA_PLACE_WAVE_MAJOR the heaviest
-                                          trajectories get those SIMDs                      */
-#define SSA_PLACE_FEED_WAVE0 16        /* 512-thread workgroups: the producer wave that feeds
-                                          event-loop wave 0 issues ahead of event-loop waves
-                                          1-3 (wave priorities), so wave 0 keeps its draws
-                                          while the chip is busy                            */
-#define SSA_PLACE_PRODUCER_FIRST 32    /* 512-thread workgroups: producer waves issue ahead of
-                                          event-loop waves (a producer stops at a full ring) */
-#define SSA_PLACE_DEDICATED_FEED0 64   /* 512-thread workgroups: three event-loop waves; wave 0
-                                          alone on its SIMD and its producer alone on the
-                                          next, the other two fed from their own SIMDs (with
-                                          SSA_PLACE_WAVE_MAJOR: the heaviest trajectories on
-                                          wave 0, never short of draws)                    */
-#define SSA_PLACE_TWO_FEED0 128        /* with SSA_PLACE_DEDICATED_FEED0, one-item launches
-                                          (SSA_E_INVALID otherwise): two producer waves share
-                                          wave 0's draws, one the even and one the odd event
-                                          indices (a lone event loop on the conversion path
-                                          uses draws faster than one producer makes them);
-                                          no effect where the draw ring holds fewer than 4
-                                          slots (the largest networks)                     */
+#define SSA_PLACE_NEIGHBOUR_PRODUCER 2 /* no effect                                          */
+#define SSA_PLACE_WAVE_MAJOR 4         /* up to 256 threads, single-item runs: each launch's
+                                          first claims are static, wave-major (the first 64
+                                          claims of the claim order go to wave 0 of workgroup
+                                          0, the next to wave 0 of workgroup 1, ...), so after
+                                          a reordering window the heaviest trajectories share
+                                          one wave per workgroup                             */
+#define SSA_PLACE_SOLO_WAVE0 8         /* no effect; one-item launches (SSA_E_INVALID
+                                          otherwise)                                         */
+#define SSA_PLACE_FEED_WAVE0 16        /* no effect                                          */
+#define SSA_PLACE_PRODUCER_FIRST 32    /* no effect                                          */
+#define SSA_PLACE_DEDICATED_FEED0 64   /* no effect                                          */
+#define SSA_PLACE_TWO_FEED0 128        /* no effect; with SSA_PLACE_DEDICATED_FEED0, one-item
+                                          launches (SSA_E_INVALID otherwise)                 */
 
 typedef struct ssa_run_desc {
     const ssa_item *items;
@@ -335,8 +322,8 @@ typedef struct ssa_tune_result {
 /* Launch-shape autotuner. Runs desc's workload (into scratch outputs owned by
  * the library; desc's output pointers are ignored) once per candidate shape:
  * block size 64 or 256; grid holding 1, 2 or 4 waves per SIMD with lane
- * refill, or one lane per trajectory, and 512 (producer waves) with one
- * workgroup per CU; one launch, 4 even snapshot windows, a first window of a
+ * refill, or one lane per trajectory, and 512 (the pipelined kernel) with one
+ * workgroup and two per CU; one launch, 4 even snapshot windows, a first window of a
  * tenth of the rows followed by 1 or 2 windows, or of 15% or 20% of the rows
  * followed by 1. Times
  * each with HIP events, keeps the fastest in memory and in

@@ -29,6 +29,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <fstream>
+#include <functional>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -134,6 +135,25 @@ int mass_action_total_order(const Model &md, int j)
     for (int s = 0; s < md.N; ++s)
         t += md.order[(size_t)j * md.N + s];
     return t;
+}
+
+// Largest constant of reaction j with which a product of its factors that
+// holds a zero factor is zero without a test of the counts: no partial product
+// before the zero factor overflows (infinity times zero is not zero). A count
+// x below the order o gives x (x - 1) ... <= 6 before its zero factor; another
+// species' factors may each be any count (fp16 keeps its guards there).
+double unguarded_limit(int fmt, const Model &md, int j)
+{
+    const double top = fmt == SSA_FMT_FP64 ? 1.7e308 : fmt == SSA_FMT_FP16 ? 65504.0 : 3.3e38;
+    const int tot = mass_action_total_order(md, j);
+    if (md.law[j].kind != SSA_LAW_MASS_ACTION || tot == 0)
+        return INFINITY;
+    int reactants = 0;
+    for (int s = 0; s < md.N; ++s)
+        reactants += md.order[(size_t)j * md.N + s] > 0;
+    if (reactants > 1 && fmt == SSA_FMT_FP16)
+        return INFINITY;
+    return reactants > 1 ? top / std::ldexp(1.0, 31 * tot) : top / 8.0;
 }
 
 // Rounding ops of reaction j: count conversions (conversion slots) and the
@@ -253,12 +273,26 @@ std::string gen_model(const Model &md, int idx, uint64_t record_mask)
     int lo_max = 0;
     for (int s = 0; s < md.N; ++s)
         lo_max = std::max(lo_max, lo[(size_t)s]);
+    int d_max = 0;
+    bool multi = false;   // some mass-action reaction takes two species
+    for (int j = 0; j < md.M; ++j) {
+        int reactants = 0;
+        for (int s = 0; s < md.N; ++s) {
+            d_max = std::max(d_max, (int)md.nu[(size_t)j * md.N + s]);
+            reactants += md.order[(size_t)j * md.N + s] > 0;
+        }
+        multi = multi || (md.law[j].kind == SSA_LAW_MASS_ACTION && reactants > 1);
+    }
     std::ostringstream o;
     o << "struct Md" << idx << " {\n"
       << "  static constexpr int N = " << md.N << ", M = " << md.M << ", NPROP = " << nprop << ", NCONV = " << nconv
       << ";\n"
       << "  static constexpr u64 REC = " << record_mask << "ull;  // reactions whose firings are recorded\n"
       << "  static constexpr int LO_MAX = " << lo_max << ";  // largest reactant order of a species\n"
+      << "  static constexpr int DMAX = " << d_max << ";  // largest increase of a count by one event\n"
+      << "  // zero guards outside the careful loop: a factor before the zero one may overflow fp16\n"
+      << "  template <class P> static constexpr bool needs_guard() { return P::NARROW && "
+      << (multi ? "true" : "false") << "; }\n"
       << "  // some count below its species' largest reactant order (a zero guard may apply);\n"
       << "  // counts are never negative, so x - lo < 0 exactly when x < lo, and the OR of\n"
       << "  // the differences is negative when one of them is (one compare for the wave)\n"
@@ -331,6 +365,35 @@ std::string gen_model(const Model &md, int idx, uint64_t record_mask)
         }
     }
     o << "    }\n";
+    // The reaction as a balanced tree of selects over past[j] (the reaction comes
+    // after j), and the state after it with one such tree per species where every
+    // state is stored: log2 M dependent selects where a count of the true ones
+    // takes M dependent additions.
+    auto tree = [](const std::vector<int> &v) {
+        std::function<std::string(int, int)> go = [&](int lo, int hi) -> std::string {
+            bool same = true;
+            for (int j = lo; j <= hi; ++j)
+                same = same && v[(size_t)j] == v[(size_t)lo];
+            if (same)
+                return std::to_string(v[(size_t)lo]);
+            const int mid = (lo + hi) / 2;
+            return "pick(past[" + std::to_string(mid) + "], " + go(mid + 1, hi) + ", " + go(lo, mid) + ")";
+        };
+        return go(0, (int)v.size() - 1);
+    };
+    std::vector<int> index((size_t)md.M);
+    for (int j = 0; j < md.M; ++j)
+        index[(size_t)j] = j;
+    o << "  }\n"
+      << "  __device__ static __forceinline__ int reaction(const bool (&past)[M]) {\n    (void)past;\n    return "
+      << tree(index) << ";\n  }\n"
+      << "  __device__ static __forceinline__ void advance(i32 (&x)[N], const bool (&past)[M]) {\n    (void)past;\n";
+    for (int s = 0; s < md.N && md.N <= 3; ++s) {
+        std::vector<int> nu((size_t)md.M);
+        for (int j = 0; j < md.M; ++j)
+            nu[(size_t)j] = md.nu[(size_t)j * md.N + s];
+        o << "    x[" << s << "] += " << tree(nu) << ";\n";
+    }
     // x += nu_mu, mu in [0, M] (mu = M: nothing fires). A species whose net
     // changes fit W-bit signed fields for all M + 1 values of mu reads its
     // change from one packed constant with a single bitfield extract; any other
@@ -404,154 +467,62 @@ std::string gen_source(const std::vector<const Model *> &models, const ModeSpec 
       << "extern \"C\" __global__ void __launch_bounds__(256) ssa_kernel(LaunchArgs L) {\n"
       << "  const u32 wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;\n"
       << "  const u32 slot_rank = (threadIdx.x >> 6) * gridDim.x + blockIdx.x, n_slots = gridDim.x * (blockDim.x >> 6);\n"
-      << "  SelfFeed feed;\n"
       << "  u32 it = wave % SSA_N_ITEMS;\n"
       << "  for (u32 i = 0; i < SSA_N_ITEMS; ++i) {\n"
       << "    switch (it) {\n";
     for (size_t i = 0; i < models.size(); ++i)
         o << "    case " << i << ": run_item<PrecRun, Md" << i << ", " << (per_lane_rates[i] ? "true" : "false")
-          << ">(L, L.item[" << i << "], feed, slot_rank, n_slots); break;\n";
+          << ">(L, L.item[" << i << "], slot_rank, n_slots); break;\n";
     o << "    default: break;\n"
       << "    }\n"
       << "    it = it + 1 == SSA_N_ITEMS ? 0 : it + 1;\n"
       << "  }\n"
       << "}\n";
-    // 512-thread workgroups: waves 0-3 run the event loop, wave w + 4 (on the
-    // same SIMD as wave w) forms wave w's draws ahead into an LDS ring
-    o << "constexpr int SSA_RING_NW = ";
+    int m_max = 0;
     for (size_t i = 0; i < models.size(); ++i)
-        o << (i ? ", " : "") << (i + 1 < models.size() ? "cmax(" : "")
-          << "RingWords<PrecRun, Md" << i << ">::NW";
-    for (size_t i = 1; i < models.size(); ++i)
-        o << ")";
-    o << ";\n"
-      << "constexpr int SSA_RING_D = ring_depth(SSA_RING_NW);\n"
-      << "// 512 threads are two waves per SIMD: at most 256 registers (VGPRs and AGPRs\n"
-      << "// together) per wave, which the waves-per-EU bound makes the compiler keep\n"
-      << "extern \"C\" __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))\n"
-      << "ssa_kernel_pc(LaunchArgs L) {\n"
-      << "  // wave index made wave-uniform: role branches are scalar branches, so the\n"
-      << "  // SALU work of one role (priorities, sleeps) never runs in another role's wave\n"
-      << "  const u32 w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();\n"
-      << "  // event-loop wave c (= w for w < 4) is fed by the producer wave on its own\n"
-      << "  // SIMD (w = c + 4) or, with PLACE_NEIGHBOUR, on the next one (w = 4 + (c + 1) % 4).\n"
-      << "  // PLACE_DEDICATED: event-loop waves 0, 2, 3; wave 0 alone on SIMD 0 and its\n"
-      << "  // producer (wave 5) alone on SIMD 1; waves 2 and 3 fed from their own SIMDs\n"
-      << "  const bool ded = (L.place & PLACE_DEDICATED) != 0u;\n"
-      << "  const u32 c = w < 4u ? w\n"
-      << "              : ded ? (w == 5u ? 0u : w == 4u ? 1u : w - 4u)\n"
-      << "                    : ((w + ((L.place & (PLACE_NEIGHBOUR | PLACE_SOLO0)) ? 3u : 0u)) & 3u);\n"
-      << "  if constexpr (SSA_RING_D == 0) {\n"
-      << "    SelfFeed feed;\n"
-      << "    const u32 slot_rank = w * gridDim.x + blockIdx.x, n_slots = gridDim.x * 8u;\n"
-      << "    u32 it = (blockIdx.x * 8u + w) % SSA_N_ITEMS;\n"
-      << "    for (u32 i = 0; i < SSA_N_ITEMS; ++i) {\n"
-      << "      switch (it) {\n";
-    for (size_t i = 0; i < models.size(); ++i)
-        o << "      case " << i << ": run_item<PrecRun, Md" << i << ", " << (per_lane_rates[i] ? "true" : "false")
-          << ">(L, L.item[" << i << "], feed, slot_rank, n_slots); break;\n";
-    o << "      default: break;\n"
-      << "      }\n"
-      << "      it = it + 1 == SSA_N_ITEMS ? 0 : it + 1;\n"
-      << "    }\n"
-      << "    return;\n"
-      << "  } else {\n"
-      << "  __shared__ RingCtl ctl[4];\n"
-      << "  __shared__ u32 ring[4 * (SSA_RING_D > 0 ? SSA_RING_D : 1) * SSA_RING_NW * 64];\n"
-      << "  if (w < 4) {\n"
-      << "    ctl[c].convw[lane] = 0u;\n"
-      << "    ctl[c].req_e[lane] = 0u;\n"
-      << "    ctl[c].done[lane] = 0u;\n"
-      << "    ctl[c].item = 0u;\n"
-      << "  } else {\n"
-      << "    ctl[c].made[0][lane] = 0u;\n"
-      << "    ctl[c].made[1][lane] = 0u;\n"
-      << "  }\n"
-      << "  __syncthreads();\n"
-      << "  u32 *my_ring = ring + c * (SSA_RING_D * SSA_RING_NW * 64);\n"
-      << "  u32 it = (blockIdx.x * 4u + c) % SSA_N_ITEMS;\n"
-      << "  const bool solo0 = SSA_N_ITEMS == 1 && (L.place & PLACE_SOLO0) != 0u && !ded;\n"
-      << "  // PLACE_TWO0 (with PLACE_DEDICATED, one-item launches): wave 1 is a second\n"
-      << "  // producer of wave 0; waves 5 and 1 make its draws of even and odd index\n"
-      << "  // (a ring of fewer than 4 slots, for the largest networks, keeps one producer)\n"
-      << "  const bool two = SSA_N_ITEMS == 1 && SSA_RING_D >= 4 && ded && (L.place & PLACE_TWO0) != 0u;\n"
-      << "  // event-loop slots (the wave-major static claims go in slot order, heaviest\n"
-      << "  // first): with PLACE_DEDICATED three per workgroup (waves 0, 2, 3); with\n"
-      << "  // PLACE_FEED0 wave 1, which shares its SIMD with wave 0's producer, comes last\n"
-      << "  const bool feed0 = (L.place & PLACE_FEED0) != 0u;\n"
-      << "  const u32 ev_rank = ded ? (c == 0u ? 0u : c - 1u) : feed0 ? (c == 0u ? 0u : c == 1u ? 3u : c - 1u) : c;\n"
-      << "  const u32 ev_per_wg = ded ? 3u : 4u;\n"
-      << "  // wave priorities: event-loop waves 3, producers 0; PLACE_PRODUCER_FIRST:\n"
-      << "  // producers 3, event-loop waves 2; PLACE_FEED0: wave 0 and its producer 3,\n"
-      << "  // event-loop waves 1-3 2, the other producers 0\n"
-      << "  const bool pfirst = (L.place & PLACE_PRODUCER_FIRST) != 0u;\n"
-      << "  const bool ev_low = pfirst || ((L.place & PLACE_FEED0) != 0u && c != 0u);\n"
-      << "  const bool pr_high = pfirst || ((L.place & PLACE_FEED0) != 0u && c == 0u);\n"
-      << "  // PLACE_SOLO0 (one-item launches): event-loop wave 3 forms its own draws; a\n"
-      << "  // second copy of the event loop per network, so it is compiled only for one\n"
-      << "  // network (several networks' copies would crowd the instruction cache)\n"
-      << "#if SSA_N_ITEMS == 1\n"
-      << "  if (w < 4 && solo0 && c == 3u) {\n"
-      << "    if (ev_low) __builtin_amdgcn_s_setprio(2); else __builtin_amdgcn_s_setprio(3);\n"
-      << "    SelfFeed feed;\n"
-      << "    const u32 slot_rank = ev_rank * gridDim.x + blockIdx.x, n_slots = gridDim.x * 4u;\n"
-      << "    for (u32 i = 0; i < SSA_N_ITEMS; ++i) {\n"
-      << "      switch (it) {\n";
-    for (size_t i = 0; i < models.size(); ++i)
-        o << "      case " << i << ": run_item<PrecRun, Md" << i << ", " << (per_lane_rates[i] ? "true" : "false")
-          << ">(L, L.item[" << i << "], feed, slot_rank, n_slots); break;\n";
-    o << "      default: break;\n"
-      << "      }\n"
-      << "      it = it + 1 == SSA_N_ITEMS ? 0 : it + 1;\n"
-      << "    }\n"
-      << "  } else if (two && (w == 1u || w == 5u)) {\n"
-      << "    if constexpr (SSA_RING_D >= 4) {\n"
-      << "      if (pfirst || feed0) __builtin_amdgcn_s_setprio(3);\n"
-      << "      produce_item<PrecRun, Md0, SSA_RING_D, SSA_RING_NW, 2>(L, L.item[0], &ctl[0], ring, 0u, w == 1u ? 1u : 0u);\n"
-      << "    }\n"
-      << "  } else if (two && w == 0u) {   // the event loop fed by both\n"
-      << "    if constexpr (SSA_RING_D >= 4) {\n"
-      << "      if (ev_low) __builtin_amdgcn_s_setprio(2); else __builtin_amdgcn_s_setprio(3);\n"
-      << "      RingFeed<SSA_RING_D, SSA_RING_NW, true> feed{&ctl[0], ring, lane, 0u, 0u, &ctl[0].made[0][lane]};\n"
-      << "      lds_st(&ctl[0].item, 0u);\n"
-      << "      lgkm_wait();\n"
-      << "      run_item<PrecRun, Md0, " << (per_lane_rates[0] ? "true" : "false")
-      << ">(L, L.item[0], feed, blockIdx.x, gridDim.x * ev_per_wg);\n"
-      << "      lds_st(&ctl[0].item, ~0u);\n"
-      << "    }\n"
-      << "  } else\n"
-      << "#endif\n"
-      << "  if (w < 4 && !(ded && w == 1u)) {   // PLACE_DEDICATED: wave 1 leaves SIMD 1 to wave 5\n"
-      << "    if (ev_low) __builtin_amdgcn_s_setprio(2); else __builtin_amdgcn_s_setprio(3);\n"
-      << "    RingFeed<SSA_RING_D, SSA_RING_NW> feed{&ctl[c], my_ring, lane, 0u, 0u, &ctl[c].made[0][lane]};\n"
-      << "    const u32 slot_rank = ev_rank * gridDim.x + blockIdx.x, n_slots = gridDim.x * ev_per_wg;\n"
-      << "    for (u32 i = 0; i < SSA_N_ITEMS; ++i) {\n"
-      << "      lds_st(&ctl[c].item, i);\n"
-      << "      lgkm_wait();\n"
-      << "      switch (it) {\n";
-    for (size_t i = 0; i < models.size(); ++i)
-        o << "      case " << i << ": run_item<PrecRun, Md" << i << ", " << (per_lane_rates[i] ? "true" : "false")
-          << ">(L, L.item[" << i << "], feed, slot_rank, n_slots); break;\n";
-    o << "      default: break;\n"
-      << "      }\n"
-      << "      it = it + 1 == SSA_N_ITEMS ? 0 : it + 1;\n"
-      << "    }\n"
-      << "    lds_st(&ctl[c].item, ~0u);\n"
-      << "  } else if (w >= 4u && !((solo0 || ded) && w == 4u)) {   // PLACE_SOLO0, PLACE_DEDICATED: wave 4 leaves SIMD 0 to wave 0\n"
-      << "    if (pr_high) __builtin_amdgcn_s_setprio(3);\n"
-      << "    for (u32 i = 0; i < SSA_N_ITEMS; ++i) {\n"
-      << "      switch (it) {\n";
-    for (size_t i = 0; i < models.size(); ++i)
-        o << "      case " << i << ": produce_item<PrecRun, Md" << i
-          << ", SSA_RING_D, SSA_RING_NW, 1>(L, L.item[" << i << "], &ctl[c], my_ring, i, 0u); break;\n";
-    o << "      default: break;\n"
-      << "      }\n"
-      << "      it = it + 1 == SSA_N_ITEMS ? 0 : it + 1;\n"
-      << "    }\n"
-      << "  }\n"
-      << "  }\n"
-      << "}\n"
-      << "extern \"C\" __global__ void ssa_fill_u32(u32 *p, u32 n, u32 v) {\n"
+        m_max = std::max(m_max, models[i]->M);
+    // pipelined event loop: one workgroup to a CU (ssa_kernel_pl) and two (ssa_kernel_ph)
+    for (int half = 0; half < 2; ++half) {
+        const std::string h = half ? "true" : "false";
+        o << "extern \"C\" __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu("
+          << (m_max <= 16 ? "4, 4" : "2, 2") << ")))\n"
+          << (half ? "ssa_kernel_ph" : "ssa_kernel_pl") << "(LaunchArgs L) {\n"
+          << "  if constexpr (true";
+        for (size_t i = 0; i < models.size(); ++i)
+            o << " && PipeGeom<PrecRun, Md" << i << ", " << h << ">::OK";
+        o << ") {\n"
+          << "  __shared__ PipeCtl ctl;\n"
+          << "  __shared__ typename PrecRun::Tm snap_t[kSnapTable + 2];\n"
+          << "  extern __shared__ __attribute__((aligned(16))) u32 lds[];\n"
+          << "  const u32 w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();\n"
+          << "  // waves w and w + 4 share a SIMD; the second workgroup of a CU takes its event and\n"
+          << "  // clock waves to the other two SIMDs\n"
+          << "  const u32 role = blockIdx.x >= L.pipe_half ? (w & 4u) | ((w + 2u) & 3u) : w;\n"
+          << "  for (i32 i = (i32)threadIdx.x; i < kSnapTable + 2; i += 512)\n"
+          << "    snap_t[i] = L.k_lo + i < L.k_hi ? snap_time<PrecRun>(L, L.k_lo + i) : (PrecRun::Tm)SSA_INF_F;\n"
+          << "  PipeWg W = {&ctl, lds, lds, 0u, (const u32 *)snap_t};\n"
+          << "  u32 it = blockIdx.x % SSA_N_ITEMS;\n"
+          << "  for (u32 i = 0; i < SSA_N_ITEMS; ++i) {\n"
+          << "    if (w == 0u) {\n"
+          << "      if (lane < (u32)kPipeBatches) ctl.ready[lane] = 0u;\n"
+          << "      ctl.done_e = 0u; ctl.done_c = 0u; ctl.done_s = 0u - 1024u; ctl.next = 0u; ctl.leave = 0u;\n"
+          << "      ctl.gen = 0u; ctl.convw = 0u; ctl.sw = 0u;\n"
+          << "    }\n"
+          << "    __syncthreads();\n"
+          << "    switch (it) {\n";
+        for (size_t i = 0; i < models.size(); ++i)
+            o << "    case " << i << ": pipe_item<PrecRun, Md" << i << ", " << h << ", "
+              << (per_lane_rates[i] ? "true" : "false") << ">(L, L.item[" << i
+              << "], W, L.pipe_words, role); break;\n";
+        o << "    default: break;\n"
+          << "    }\n"
+          << "    __syncthreads();\n"
+          << "    it = it + 1 == SSA_N_ITEMS ? 0 : it + 1;\n"
+          << "  }\n"
+          << "  }\n"
+          << "}\n";
+    }
+    o << "extern \"C\" __global__ void ssa_fill_u32(u32 *p, u32 n, u32 v) {\n"
       << "  u32 i = blockIdx.x * blockDim.x + threadIdx.x;\n"
       << "  if (i < n) p[i] = v;\n"
       << "}\n";
@@ -752,20 +723,23 @@ struct SourceId {
     size_t size = 0;
 };
 
+// dynamic LDS of a pipelined workgroup with a CU to itself, and with half of one
+// (kPipeLds, kPipeLdsHalf in ssa_device.hip)
+constexpr unsigned kPipeLds = 150 * 1024, kPipeLdsHalf = 75 * 1024;
+
 struct Loaded {
     hipModule_t mod = nullptr;
     hipFunction_t kernel = nullptr;
-    hipFunction_t kernel_pc = nullptr;   // 512-thread workgroups: event-loop waves paired with draw producers
+    // pipelined event loop (512 threads): one workgroup to a CU, two to a CU (ok: its
+    // ring fits, and as many are resident)
+    hipFunction_t kernel_pl = nullptr, kernel_ph = nullptr;
+    bool pl_ok = false, ph_ok = false;
     hipFunction_t fill = nullptr;
     hipFunction_t rg_hist = nullptr, rg_scan = nullptr, rg_scatter = nullptr;
-    int vgprs = -1, vgprs_pc = -1;
-    // dynamic LDS added to each ssa_kernel_pc workgroup (unused by the kernel) so
-    // that it holds more than half of a CU's LDS: one workgroup, i.e. one
-    // event-loop wave per SIMD, per CU, whatever the dispatcher would pack
-    unsigned pc_lds_pad = 0;
+    int vgprs = -1, vgprs_pl = -1, vgprs_ph = -1;
     int cus = 0;
-    int per_cu[5] = {};   // resident workgroups per CU of 64, 128, 192 and 256 threads, and of ssa_kernel_pc
-    int resident(int block) const { return per_cu[block == 512 ? 4 : block / 64 - 1]; }
+    int per_cu[4] = {};   // resident workgroups per CU of 64, 128, 192 and 256 threads
+    int resident(int block) const { return per_cu[block / 64 - 1]; }
 };
 
 std::mutex g_jit_mu;
@@ -826,29 +800,31 @@ int get_kernel(const ssa_run_desc *d, const SourceId &id, Loaded &out, bool load
     Loaded ld;
     HIP_TRY(hipModuleLoadData(&ld.mod, code.data()));
     HIP_TRY(hipModuleGetFunction(&ld.kernel, ld.mod, "ssa_kernel"));
-    HIP_TRY(hipModuleGetFunction(&ld.kernel_pc, ld.mod, "ssa_kernel_pc"));
+    HIP_TRY(hipModuleGetFunction(&ld.kernel_pl, ld.mod, "ssa_kernel_pl"));
+    HIP_TRY(hipModuleGetFunction(&ld.kernel_ph, ld.mod, "ssa_kernel_ph"));
     HIP_TRY(hipModuleGetFunction(&ld.fill, ld.mod, "ssa_fill_u32"));
     HIP_TRY(hipModuleGetFunction(&ld.rg_hist, ld.mod, "ssa_regroup_hist"));
     HIP_TRY(hipModuleGetFunction(&ld.rg_scan, ld.mod, "ssa_regroup_scan"));
     HIP_TRY(hipModuleGetFunction(&ld.rg_scatter, ld.mod, "ssa_regroup_scatter"));
-    int regs = -1;
-    if (hipFuncGetAttribute(&regs, HIP_FUNC_ATTRIBUTE_NUM_REGS, ld.kernel) == hipSuccess)
-        ld.vgprs = regs;
-    regs = -1;
-    if (hipFuncGetAttribute(&regs, HIP_FUNC_ATTRIBUTE_NUM_REGS, ld.kernel_pc) == hipSuccess)
-        ld.vgprs_pc = regs;
-    int lds_cu = 0, lds_block = 0, lds_static = 0;
-    if (hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) == hipSuccess &&
-        hipDeviceGetAttribute(&lds_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess &&
-        hipFuncGetAttribute(&lds_static, HIP_FUNC_ATTRIBUTE_SHARED_SIZE_BYTES, ld.kernel_pc) == hipSuccess) {
-        const int want = lds_cu / 2 + 1024;
-        if (want > lds_static && want <= lds_block)
-            ld.pc_lds_pad = (unsigned)(want - lds_static);
-    }
+    auto registers = [](hipFunction_t f) {
+        int regs = -1;
+        return hipFuncGetAttribute(&regs, HIP_FUNC_ATTRIBUTE_NUM_REGS, f) == hipSuccess ? regs : -1;
+    };
+    ld.vgprs = registers(ld.kernel);
+    ld.vgprs_pl = registers(ld.kernel_pl);
+    ld.vgprs_ph = registers(ld.kernel_ph);
     HIP_TRY(hipDeviceGetAttribute(&ld.cus, hipDeviceAttributeMultiprocessorCount, dev));
     for (int i = 0; i < 4; ++i)
         HIP_TRY(hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&ld.per_cu[i], ld.kernel, 64 * (i + 1), 0));
-    HIP_TRY(hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&ld.per_cu[4], ld.kernel_pc, 512, ld.pc_lds_pad));
+    // a pipelined kernel whose ring does not fit is empty: it has no static LDS
+    auto fits = [](hipFunction_t f, unsigned lds, int want) {
+        int lds_static = 0, n = 0;
+        return hipFuncGetAttribute(&lds_static, HIP_FUNC_ATTRIBUTE_SHARED_SIZE_BYTES, f) == hipSuccess &&
+               lds_static > 0 &&
+               hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 512, lds) == hipSuccess && n >= want;
+    };
+    ld.pl_ok = fits(ld.kernel_pl, kPipeLds, 1);
+    ld.ph_ok = fits(ld.kernel_ph, kPipeLdsHalf, 2);
     g_loaded[key] = ld;
     out = ld;
     return SSA_OK;
@@ -952,7 +928,8 @@ struct LaunchArgsHead {
     int32_t k_lo, k_hi;
     int32_t first, last;
     uint32_t seed_lo, seed_hi;
-    uint32_t place, place_pad;
+    uint32_t place, guard;
+    uint32_t pipe_words, pipe_half;
     uint64_t max_events;
 };
 
@@ -1152,7 +1129,10 @@ struct ssa_run {
     int n_launch = 0;
     int first_window = 0;  // snapshot rows of the first chunk (0: even windows)
     int block = 0, grid = 0, vgprs = -1;
-    int place = 0;        // PLACE_* bits of the launches
+    int place = 0;        // SSA_PLACE_* flags of the launches
+    bool pipe = false;        // the pipelined kernel
+    bool pipe_two = false;    // its workgroups come two to a CU
+    bool guard = false;       // a rate constant is so large that zero guards matter
     bool graph = false;
     std::vector<ItemBuf> items;
     std::vector<std::pair<void *, size_t>> owned;  // library-owned device buffers (returned to the cache)
@@ -1332,7 +1312,10 @@ int launch_all(ssa_run *r, const ssa_run_desc *d, const Loaded &ld, int n_chunks
     A.h.seed_lo = (uint32_t)d->seed;
     A.h.seed_hi = (uint32_t)(d->seed >> 32);
     A.h.max_events = d->max_events;
-    A.h.place = (uint32_t)r->place;
+    A.h.place = r->place & SSA_PLACE_WAVE_MAJOR ? 2 : 0;   // PLACE_WAVE_MAJOR
+    A.h.guard = r->guard ? 1u : 0u;
+    A.h.pipe_words = (r->pipe_two ? kPipeLdsHalf : kPipeLds) / 4;
+    A.h.pipe_half = (uint32_t)ld.cus;
     const int nI = d->n_items;
     hipStream_t s = r->graph ? r->cap : r->stream;
     // one zeroed counter per (chunk, item)
@@ -1378,8 +1361,11 @@ int launch_all(ssa_run *r, const ssa_run_desc *d, const Loaded &ld, int n_chunks
         void *args[] = {&A};
         if (!r->kev.empty())
             HIP_TRY(hipEventRecord(r->kev[2 * c], s));
-        HIP_TRY(hipModuleLaunchKernel(r->block == 512 ? ld.kernel_pc : ld.kernel, r->grid, 1, 1, r->block, 1, 1,
-                                      r->block == 512 ? ld.pc_lds_pad : 0u, s, args, nullptr));
+        if (r->pipe)
+            HIP_TRY(hipModuleLaunchKernel(r->pipe_two ? ld.kernel_ph : ld.kernel_pl, r->grid, 1, 1, 512, 1, 1,
+                                          r->pipe_two ? kPipeLdsHalf : kPipeLds, s, args, nullptr));
+        else
+            HIP_TRY(hipModuleLaunchKernel(ld.kernel, r->grid, 1, 1, r->block, 1, 1, 0, s, args, nullptr));
         if (!r->kev.empty())
             HIP_TRY(hipEventRecord(r->kev[2 * c + 1], s));
         // claim order for the next chunk: heaviest trajectories of this chunk first
@@ -1499,6 +1485,7 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
             for (int j = 0; j < md.M; ++j) {
                 double k = it.set_rates ? it.set_rates[sidx * md.M + j] : md.law[j].k;
                 double v = to_prop_type(d->format, primary_constant(md, j, k));
+                r->guard = r->guard || !(v <= unguarded_limit(d->format, md, j));
                 if (wide)
                     ((double *)rt)[sidx * md.M + j] = v;
                 else
@@ -1576,24 +1563,46 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
 
     // launch shape: enough waves to cover the ensemble, at most what stays resident
     const int cus = ld.cus;
-    r->block = d->block_size ? d->block_size : (have_tuned ? tuned.block : 256);
-    if (r->block == 512)
-        r->vgprs = ld.vgprs_pc;
-    const int per_cu = ld.resident(r->block);
-    // a workgroup that cannot be resident at all (registers or LDS beyond a
-    // CU's) would fail at dispatch: refuse it here
-    if (per_cu < 1)
-        return fail(SSA_E_UNSUPPORTED, "the kernel for these networks needs more registers or LDS than one " +
-                                           std::to_string(r->block) + "-thread workgroup per CU allows; use a smaller "
-                                           "block_size (or 0)");
-    // lanes running the event loop per workgroup (half of a 512-thread one)
-    const int loop_lanes = r->block == 512 ? 256 : r->block;
-    int64_t need = (total + loop_lanes - 1) / loop_lanes;
-    int64_t resident = (int64_t)per_cu * cus;
-    int64_t grid = d->grid_size ? d->grid_size
-                                : (have_tuned && tuned.block == r->block ? tuned.grid
-                                                                          : std::max<int64_t>(1, std::min(need, resident)));
-    r->grid = (int)grid;
+    r->block = d->block_size ? d->block_size : (have_tuned ? tuned.block : 512);
+    bool mixed = d->n_items > 1;   // chains of unequal length
+    for (int i = 0; i < d->n_items; ++i)
+        mixed |= d->items[i].set_rates && d->items[i].n_sets > 1;
+    const int asked = d->grid_size ? d->grid_size : (have_tuned && tuned.block == r->block ? tuned.grid : 0);
+    // 512: the pipelined kernel, which also is the default; a network whose ring does
+    // not fit a CU's LDS runs one wave per 64 trajectories throughout
+    r->pipe = r->block == 512 && ld.pl_ok;
+    if (r->pipe) {
+        // A workgroup runs 64 trajectories at a time; a grid size asked for counts 256.
+        // Up to one workgroup per CU each has a CU to itself, where a chain of events is
+        // fastest. Beyond that two share a CU if its SIMDs would idle otherwise: the
+        // event wave of a 16-bit mode is the slower part (dimer, many full waves: 346
+        // cycles per 64 events of a CU alone, 222 in two; 1M telegraph trajectories 52.6
+        // and 29.7 ms), in FP64 the draws are, which already keep the SIMDs busy (200
+        // alone, 203-224 in two). Alone is better where the ends are long and ragged, each
+        // lane then having half as many waves beside it: FP64 in the first two rounds
+        // (Schloegl, 33,000: 1.8 and 2.3 ms), and sweeps or several networks, whose
+        // chains differ most, in the first eight (64k-trajectory dimer sweep 27.7 and 49.4
+        // ms, five networks of 20k 117 and 125; at 12 rounds 2.32 and 2.30).
+        int64_t wgs = std::max<int64_t>(1, (total + 63) / 64);
+        if (asked)
+            wgs = std::min<int64_t>(wgs, 4 * (int64_t)asked);
+        const int64_t rounds_alone = asked ? 1 : mixed ? 8 : wide ? 2 : 1;
+        r->pipe_two = ld.ph_ok && wgs > rounds_alone * cus;
+        r->grid = (int)std::min<int64_t>(wgs, r->pipe_two ? 2 * (int64_t)cus : cus);
+        r->vgprs = r->pipe_two ? ld.vgprs_ph : ld.vgprs_pl;
+    } else {
+        if (r->block == 512)
+            r->block = 256;
+        const int per_cu = ld.resident(r->block);
+        // a workgroup that cannot be resident at all (registers or LDS beyond a
+        // CU's) would fail at dispatch: refuse it here
+        if (per_cu < 1)
+            return fail(SSA_E_UNSUPPORTED, "the kernel for these networks needs more registers or LDS than one " +
+                                               std::to_string(r->block) +
+                                               "-thread workgroup per CU allows; use a smaller block_size (or 0)");
+        const int64_t need = (total + r->block - 1) / r->block;
+        r->grid = asked ? asked : (int)std::max<int64_t>(1, std::min<int64_t>(need, (int64_t)per_cu * cus));
+    }
     // placement bits: explicit (placement = SSA_PLACE_EXPLICIT | flags), else
     // the autotuned choice where the tuned block size is the one launched
     if (d->placement != 0)
@@ -1602,10 +1611,6 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
                                    SSA_PLACE_TWO_FEED0);
     else if (have_tuned && tuned.block == r->block)
         r->place = tuned.place;
-    r->place = (r->place & SSA_PLACE_NEIGHBOUR_PRODUCER ? 1 : 0) | (r->place & SSA_PLACE_WAVE_MAJOR ? 2 : 0) |
-               (r->place & SSA_PLACE_SOLO_WAVE0 ? 4 : 0) | (r->place & SSA_PLACE_FEED_WAVE0 ? 8 : 0) |
-               (r->place & SSA_PLACE_PRODUCER_FIRST ? 16 : 0) | (r->place & SSA_PLACE_DEDICATED_FEED0 ? 32 : 0) |
-               (r->place & SSA_PLACE_TWO_FEED0 ? 64 : 0);
 
     r->n_launch = n_chunks;
     if (r->noalloc) {   // direct launches, no events
@@ -1925,10 +1930,7 @@ int ssa_run_info_get(const ssa_run *run, ssa_run_info *info)
     info->total_events = tot;
     info->first_window = run->n_launch > 1 ? run->first_window : 0;
     info->graph = run->graph ? 1 : 0;
-    info->placement = SSA_PLACE_EXPLICIT | (run->place & 1 ? SSA_PLACE_NEIGHBOUR_PRODUCER : 0) |
-                      (run->place & 2 ? SSA_PLACE_WAVE_MAJOR : 0) | (run->place & 4 ? SSA_PLACE_SOLO_WAVE0 : 0) |
-                      (run->place & 8 ? SSA_PLACE_FEED_WAVE0 : 0) | (run->place & 16 ? SSA_PLACE_PRODUCER_FIRST : 0) |
-                      (run->place & 32 ? SSA_PLACE_DEDICATED_FEED0 : 0) | (run->place & 64 ? SSA_PLACE_TWO_FEED0 : 0);
+    info->placement = SSA_PLACE_EXPLICIT | run->place;
     return SSA_OK;
 }
 
@@ -1994,36 +1996,15 @@ int ssa_autotune(const ssa_run_desc *desc, ssa_tune_result *res)
             for (const ChunkOpt &ch : chunk_opts)
                 cands.push_back({block, (int)g, ch.chunks, ch.window, SSA_PLACE_EXPLICIT});
     }
-    // 512-thread workgroups: one event-loop wave per SIMD, each paired with
-    // the wave that forms its draws
-    {
-        if (ld.resident(512) >= 1) {
-            const int64_t need = std::max<int64_t>(1, (total + 255) / 256);
-            const int64_t g = std::min<int64_t>(need, cus);
-            // producers on their own or the next SIMD; claims as they come, or
-            // the first ones wave-major (one launch per item only), with wave
-            // priorities that favour wave 0's draws
-            std::vector<int> places = {SSA_PLACE_EXPLICIT, SSA_PLACE_EXPLICIT | SSA_PLACE_NEIGHBOUR_PRODUCER};
-            if (desc->n_items == 1) {
-                places.push_back(SSA_PLACE_EXPLICIT | SSA_PLACE_WAVE_MAJOR);
-                places.push_back(SSA_PLACE_EXPLICIT | SSA_PLACE_NEIGHBOUR_PRODUCER | SSA_PLACE_WAVE_MAJOR);
-                places.push_back(SSA_PLACE_EXPLICIT | SSA_PLACE_SOLO_WAVE0 | SSA_PLACE_WAVE_MAJOR);
-                // the heaviest trajectories alone on a SIMD, fed ahead of the rest
-                places.push_back(SSA_PLACE_EXPLICIT | SSA_PLACE_SOLO_WAVE0 | SSA_PLACE_WAVE_MAJOR |
-                                 SSA_PLACE_FEED_WAVE0);
-                places.push_back(SSA_PLACE_EXPLICIT | SSA_PLACE_SOLO_WAVE0 | SSA_PLACE_WAVE_MAJOR |
-                                 SSA_PLACE_PRODUCER_FIRST);
-                // three event-loop waves, wave 0 and its producer on SIMDs of their own
-                places.push_back(SSA_PLACE_EXPLICIT | SSA_PLACE_DEDICATED_FEED0 | SSA_PLACE_WAVE_MAJOR);
-                // the same with two producers for wave 0
-                places.push_back(SSA_PLACE_EXPLICIT | SSA_PLACE_DEDICATED_FEED0 | SSA_PLACE_WAVE_MAJOR |
-                                 SSA_PLACE_TWO_FEED0);
-            }
-            for (int pl : places)
-                for (const ChunkOpt &ch : chunk_opts)
-                    cands.push_back({512, (int)g, ch.chunks, ch.window, pl});
+    // the pipelined kernel, one workgroup to a CU and two
+    if (ld.pl_ok)
+        for (int per : {1, 2}) {
+            const int64_t g = std::max<int64_t>(1, (int64_t)per * cus / 4);
+            if (per == 2 && (!ld.ph_ok || total <= (int64_t)64 * cus))
+                continue;
+            for (const ChunkOpt &ch : chunk_opts)
+                cands.push_back({512, (int)g, ch.chunks, ch.window, SSA_PLACE_EXPLICIT});
         }
-    }
     cands.erase(std::unique(cands.begin(), cands.end(),
                             [](const Cand &a, const Cand &b) {
                                 return a.block == b.block && a.grid == b.grid && a.chunks == b.chunks &&

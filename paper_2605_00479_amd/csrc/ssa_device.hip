@@ -241,7 +241,7 @@ struct PrecF64 {
     typedef double T;
     typedef double A;
     typedef double Tm;
-    static constexpr bool SR = false, UNI = false, NORM = false, WIDE = true, SELECTIVE = false, NATIVE16 = false;
+    static constexpr bool SR = false, UNI = false, NORM = false, WIDE = true, SELECTIVE = false, NATIVE16 = false, NARROW = false;
     static constexpr i32 EXACT_INT = 0;   // conversions are exact: no count test
     static constexpr int SR_B = 16;
     template <bool EXACT>
@@ -262,7 +262,7 @@ struct PrecF32 {
     typedef float T;
     typedef float A;
     typedef float Tm;
-    static constexpr bool SR = false, UNI = false, NORM = false, WIDE = false, SELECTIVE = false, NATIVE16 = false;
+    static constexpr bool SR = false, UNI = false, NORM = false, WIDE = false, SELECTIVE = false, NATIVE16 = false, NARROW = false;
     static constexpr i32 EXACT_INT = 0;
     static constexpr int SR_B = 16;
     template <bool EXACT>
@@ -360,6 +360,7 @@ struct Prec16 {
     // quotient and one rounding (the compiler's fp16 division is not an IEEE
     // operation).
     static constexpr bool NATIVE16 = FMT == FMT_FP16 && !SR_OPS;
+    static constexpr bool NARROW = FMT == FMT_FP16;   // products of counts overflow
     __device__ static T mul(T a, T b, u32 rb)
     {
         if constexpr (NATIVE16)
@@ -367,7 +368,23 @@ struct Prec16 {
         else
             return rnd16<FMT, SR_OPS>(mul32<FMT>(a, b), rb);
     }
-    __device__ static T div(T a, T b, u32 rb) { return rnd16<FMT, SR_OPS>(a / b, rb); }
+    // fp16: both operands have 11 significant bits and lie in [2^-24, 2^16), or are
+    // special. One remainder correction of a times the hardware reciprocal (1 ulp) is
+    // within 2^-45 of the quotient, which lies at least 2^-36 from the middle of two
+    // binary32 values (a 2^s = b k has no solution with k odd of 25 bits), so it is
+    // the IEEE quotient; the fix-up step gives it for zeros, infinities and NaN.
+    __device__ static float quotient(float a, float b)
+    {
+        if constexpr (FMT == FMT_FP16) {
+            const float r = __builtin_amdgcn_rcpf(b);
+            const float q = a * r;
+            const float rem = __builtin_fmaf(-b, q, a);
+            return __builtin_amdgcn_div_fixupf(__builtin_fmaf(rem, r, q), b, a);
+        } else {
+            return a / b;
+        }
+    }
+    __device__ static T div(T a, T b, u32 rb) { return rnd16<FMT, SR_OPS>(quotient(a, b), rb); }
     __device__ static T add(T a, T b, u32 rb)
     {
         if constexpr (NATIVE16)
@@ -389,7 +406,9 @@ struct Prec16 {
     // -ln(u1) in {0} or [2^-24, 16.7]: the short division applies.
     __device__ static A tau_div(A l, A a0)
     {
-        if constexpr (FMT == FMT_FP16)
+        if constexpr (FMT == FMT_FP16 && UNIF)   // both rounded to fp16
+            return quotient(l, a0);
+        else if constexpr (FMT == FMT_FP16)
             return div_rn_inrange(l, a0);
         else
             return l / a0;
@@ -422,15 +441,6 @@ struct Pool {
     static constexpr int NSTREAM = NSLOT <= F0 ? 1 : 1 + (NSLOT - F0 + F1 - 1) / F1;
     static constexpr int NW = NSLOT <= 0 ? 1 : 3 + 4 * (NSTREAM - 1);
     u32 w[NW];
-    // the third word, whose bit 31 a producer sets on a draw whose ring slot
-    // also holds its conversion fields (no field uses that bit)
-    __device__ __forceinline__ u32 mark() const
-    {
-        if constexpr (NW > 2)
-            return w[2];
-        else
-            return 0u;
-    }
     // slots past the pool belong to ops that do not round stochastically
     __device__ __forceinline__ u32 hw(int s) const
     {
@@ -556,49 +566,22 @@ struct LaunchArgs {
     i32 k_lo, k_hi;          // snapshot rows written by this launch
     i32 first, last;         // first / last chunk of the run
     u32 seed_lo, seed_hi;
-    u32 place;               // PLACE_* bits (512-thread and single-item launches)
-    u32 place_pad;
+    u32 place;               // PLACE_* bits (single-item launches of ssa_kernel)
+    u32 guard;               // 1: a constant is so large that zero guards matter (pipelined kernel)
+    u32 pipe_words;          // words of the pipelined kernel's ring and tables (dynamic LDS)
+    u32 pipe_half;           // workgroups from this one on are the second of their CU
     u64 max_events;          // 0 = no cap
     ItemArgs item[SSA_N_ITEMS];
 };
 
-// Placement of work in a launch.
-//   PLACE_NEIGHBOUR: in a 512-thread workgroup the draws of event-loop wave c
-//     come from the producer wave on SIMD (c + 1) mod 4 instead of its own
-//     SIMD (waves w and w + 4 share a SIMD), so an event-loop wave whose
-//     neighbours have drained runs with its SIMD to itself.
+// Placement of work in a launch of ssa_kernel.
 //   PLACE_WAVE_MAJOR: single-item launches take their first claims
 //     statically, wave-major: claim slot r = c * gridDim.x + blockIdx.x of
-//     event-loop wave c in its workgroup holds claims [64 r, 64 r + 64) of
-//     the claim order (heaviest first after a reordering window), so the
-//     heaviest trajectories sit on wave 0 of every workgroup; the work
-//     counter starts past the static claims.
-//   PLACE_SOLO0: wave 0's SIMD holds no other wave: the producers feed the
-//     event-loop waves of the next SIMD (as PLACE_NEIGHBOUR), event-loop wave
-//     3 forms its own draws and wave 4 does not run. With PLACE_WAVE_MAJOR the
-//     heaviest trajectories then run with a SIMD to themselves from the start.
-//   PLACE_FEED0: the producer feeding event-loop wave 0 runs at wave 0's
-//     priority and event-loop waves 1-3 one below it, so that on a busy chip
-//     wave 0 (with PLACE_WAVE_MAJOR, the heaviest trajectories) keeps its draws
-//   PLACE_PRODUCER_FIRST: producer waves issue ahead of event-loop waves (a
-//     producer stops at a full ring, so it takes only what its consumer uses)
-//   PLACE_DEDICATED: three event-loop waves per workgroup; wave 0 alone on its
-//     SIMD, its producer alone on the next (waves 1 and 4 do not run), waves 2
-//     and 3 each fed by the producer on its own SIMD
-//   PLACE_TWO0 (with PLACE_DEDICATED, one-item launches): wave 1 runs as a
-//     second producer of wave 0 on SIMD 1; waves 5 and 1 make wave 0's draws
-//     of even and odd event index. A lone event-loop wave on the conversion
-//     path uses its draws faster than one producer wave makes them with their
-//     conversion fields; two waves on one SIMD also hide each other's latency.
-enum {
-    PLACE_NEIGHBOUR = 1u,
-    PLACE_WAVE_MAJOR = 2u,
-    PLACE_SOLO0 = 4u,
-    PLACE_FEED0 = 8u,
-    PLACE_PRODUCER_FIRST = 16u,
-    PLACE_DEDICATED = 32u,
-    PLACE_TWO0 = 64u
-};
+//     wave c in its workgroup holds claims [64 r, 64 r + 64) of the claim
+//     order (heaviest first after a reordering window), so the heaviest
+//     trajectories sit on wave 0 of every workgroup; the work counter starts
+//     past the static claims.
+enum { PLACE_WAVE_MAJOR = 2u };
 
 enum { ST_DONE = 0, ST_ABSORBED = 1, ST_OVERFLOW = 2, ST_CAPPED = 3, ST_SUSPENDED = 255 };
 
@@ -663,121 +646,6 @@ struct Slots {
     static constexpr int TARGET = TIME + 1;
 };
 
-// A draw as 32-bit words: the pool's words, then L and u2 (one word each in
-// binary32, two in binary64). Word k of a stored draw sits at w[S k], with S a
-// multiple of 64, so the 64 lanes of a wave touch 64 consecutive words.
-template <class P, int NSLOT>
-struct DrawIO {
-    static constexpr int NP = NSLOT > 0 ? Pool<NSLOT, P::SR_B>::NW : 0;
-    static constexpr int NA = (int)(sizeof(typename P::A) / 4);
-    static constexpr int NW = NP + 2 * NA;
-
-    template <int S>
-    __device__ static void store(u32 *w, const Draw<P, NSLOT> &d)
-    {
-        if constexpr (NP > 0) {
-#pragma unroll
-            for (int k = 0; k < NP; ++k)
-                w[S * k] = d.pool.w[k];
-        }
-        if constexpr (NA == 1) {
-            w[S * NP] = __float_as_uint((float)d.L);
-            w[S * (NP + 1)] = __float_as_uint((float)d.u2);
-        } else {
-            const u64 a = (u64)__double_as_longlong((double)d.L), b = (u64)__double_as_longlong((double)d.u2);
-            w[S * NP] = (u32)a;
-            w[S * (NP + 1)] = (u32)(a >> 32);
-            w[S * (NP + 2)] = (u32)b;
-            w[S * (NP + 3)] = (u32)(b >> 32);
-        }
-    }
-
-    // the pool's words (needed first: the propensities' rounding fields)
-    template <int S>
-    __device__ static void load_pool(const u32 *w, Draw<P, NSLOT> &d)
-    {
-        if constexpr (NP > 0) {
-#pragma unroll
-            for (int k = 0; k < NP; ++k)
-                d.pool.w[k] = w[S * k];
-        }
-    }
-
-    // L and u2 (needed later in an event than the pool)
-    template <int S>
-    __device__ static void load_tail(const u32 *w, Draw<P, NSLOT> &d)
-    {
-        if constexpr (NA == 1) {
-            d.L = __uint_as_float(w[S * NP]);
-            d.u2 = __uint_as_float(w[S * (NP + 1)]);
-        } else {
-            d.L = __longlong_as_double((long long)(((u64)w[S * (NP + 1)] << 32) | w[S * NP]));
-            d.u2 = __longlong_as_double((long long)(((u64)w[S * (NP + 3)] << 32) | w[S * (NP + 2)]));
-        }
-    }
-};
-
-// Conversion fields a producer may carry in a ring slot, after the draw's own
-// words: models whose count conversions round stochastically (R13: drawn
-// only when a count exceeds the exact-integer limit). Bit 31 of the third
-// pool word marks a draw whose slot holds them.
-template <class P, class Md>
-struct ConvRing {
-    static constexpr bool ON = P::SR && !P::SELECTIVE && Md::NCONV > 0;
-    static constexpr int NW = ON ? 4 * ConvPool<Md::NCONV, P::SR_B>::NSTREAM : 0;
-    static constexpr u32 MARK = 0x80000000u;
-};
-
-// Words of one ring slot for a model: the draw, then its conversion fields.
-template <class P, class Md>
-struct RingWords {
-    static constexpr int NW = DrawIO<P, Slots<P, Md>::NSLOT>::NW + ConvRing<P, Md>::NW;
-};
-
-// --------------------------------------------------------------------------
-// Draw feeds. The event loop takes event n + 1's draw while it runs event n.
-// SelfFeed forms it in the same wave. RingFeed takes it from a ring in LDS
-// that a producer wave on the same SIMD fills ahead (produce_item), and forms
-// it itself wherever the ring does not hold it: the event loop never waits
-// for the producer. The producer makes exactly the draws the loop would form
-// (same function of seed, trajectory and event index), so results do not
-// depend on the feed.
-//
-// Protocol, per lane (consumer lane l and producer lane l of the paired waves).
-// A counter word is (low 24 bits of an event index) << 8 | epoch, so a lane
-// steps it by adding 256 and the 24-bit index wraps without touching the epoch:
-//   req_*  consumer -> producer: trajectory id and claim event index, then the
-//          epoch e (1..255, new at every claim) once the rest is written;
-//   done   consumer -> producer: counter word of the first draw the consumer
-//          has not read yet;
-//   made   producer -> consumer: counter word of the first draw not made yet;
-//          draws [made - D, made) of epoch e are in the ring (the consumer
-//          resets it at a claim, before publishing the epoch). With two
-//          producers for one consumer (PLACE_TWO0), producer k makes the draws
-//          of odd (k = 1) or even (k = 0) event index and publishes made[k]:
-//          its draws of that parity in [made[k] - D, made[k]) are in the ring,
-//          and the consumer reads the made word of its next draw's parity.
-//   convw  consumer -> producer: the lane's counts need conversion fields
-//          (reset at a claim); the producer then also forms each draw's
-//          conversion fields, stores them after the draw's words, and marks
-//          the draw by bit 31 of its third pool word (a bit no field uses).
-// The producer writes draw p only while p < done + D, so a draw the consumer
-// finds made stays in place until it has read it. Ordering rests on waits for
-// completed LDS operations (lgkmcnt 0): the producer waits for its ring
-// stores before it updates made, the consumer waits for its made load before
-// it loads ring words, and for its ring loads before it updates done.
-// --------------------------------------------------------------------------
-struct RingCtl {
-    u32 made[2][64];   // [parity class][lane]; class 1 only with two producers
-    u32 done[64];
-    u32 req_e[64];
-    u32 req_id[64];
-    u32 req_lo[64];
-    u32 req_hi[64];
-    u32 convw[64];   // consumer -> producer: 1 while the lane's trajectory wants conversion fields
-    u32 item;        // consumer -> producer: sequence number of the item in progress (~0u: finished)
-};
-
 __device__ __forceinline__ void lgkm_wait()
 {
     __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
@@ -794,299 +662,6 @@ __device__ __forceinline__ void lds_st(u32 *p, u32 v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-struct SelfFeed {
-    static constexpr bool RING = false;
-    __device__ void claim(u32, u64) {}
-    __device__ void request_conv(u32) const {}
-};
-
-template <int D, int NWMAX, bool TWO = false>
-struct RingFeed {
-    static constexpr bool RING = true;
-    static_assert((D & (D - 1)) == 0, "ring depth is a power of two");
-    RingCtl *ctl;   // this consumer wave's control words
-    u32 *ring;      // [NWMAX][D][64]: word k of slot s, lane l at ring[(k D + s) 64 + l]
-    u32 lane;
-    u32 eb;         // epoch of the lane's trajectory (0: none claimed yet)
-    u32 dw;         // counter word of the draw the lane takes next (event n + 1)
-    // TWO (two producers, PLACE_TWO0): the made word for draw dw, formed when dw
-    // changes (its byte offset in made is the parity bit of the event index, bit
-    // 8 of a counter word), so the load at the top of the next event waits for
-    // no address arithmetic (a lone wave on the conversion path measured 679
-    // cycles per event with the address formed from dw there, 648 with it formed
-    // ahead). With one producer the made word's address is fixed: a feed type of
-    // its own keeps that arithmetic out of every other event loop (5% of the
-    // five-network batch's step).
-    const u32 *mptr;   // &ctl->made[0][lane] until the first claim
-
-    // a new trajectory on this lane; the loop forms draws n and n + 1 itself.
-    // made is reset to "nothing made in this epoch" before the epoch is
-    // published, so a made word the lane finds in its epoch was written for it
-    // (a late write from an older epoch is a few epochs behind, never a hit)
-    __device__ void claim(u32 id, u64 n)
-    {
-        eb = eb % 255u + 1u;
-        dw = ((u32)(n + 1) << 8) | eb;
-        lds_st(&ctl->done[lane], dw);
-        lds_st(&ctl->made[0][lane], dw);
-        lds_st(&ctl->made[1][lane], dw);
-        if constexpr (TWO)
-            mptr = (const u32 *)((const char *)&ctl->made[0][lane] + (dw & 0x100u));
-        lds_st(&ctl->req_id[lane], id);
-        lds_st(&ctl->req_lo[lane], (u32)n);
-        lds_st(&ctl->req_hi[lane], (u32)(n >> 32));
-        lds_st(&ctl->convw[lane], 0u);
-        lgkm_wait();
-        lds_st(&ctl->req_e[lane], eb);
-    }
-
-    // The request word: while the wave runs a version whose conversions
-    // round, each of its lanes asks the producer for every draw's conversion
-    // fields (set when the wave enters a version loop; a claim clears it).
-    // The producer forms them for the whole wave once any lane asks.
-    __device__ void request_conv(u32 on) const { lds_st(&ctl->convw[lane], on); }
-
-    // Conversion fields of the current event's draw (event n, counter word
-    // dw - 256): from its ring slot where the producer formed them with the
-    // draw (the draw came from the ring and carries the mark), formed here
-    // for the active lanes whose draw lacks the mark (a draw made before the
-    // request, or formed by the event loop); a lane whose counts are all
-    // exact ignores its fields. The slot is intact: the producer may rewrite
-    // it only once done passes event n, which read() publishes after this
-    // event's loads have completed.
-    // pre: the slot's conversion words, loaded with the draw (read_conv in the
-    // previous event; meaningful where the draw carries the mark).
-    template <int NCONV, int B>
-    __device__ ConvPool<NCONV, B> conv(const ConvPool<NCONV, B> &pre, u32 mark, u64 act, u64 n, u32 id, u32 k0,
-                                       u32 k1) const
-    {
-        ConvPool<NCONV, B> cp = pre;
-        const u64 self = act & ~lanes((i32)mark < 0);   // the mark is bit 31
-        if (__builtin_expect(self != 0, 0)) {
-            __asm__ volatile("");
-            const ConvPool<NCONV, B> f = make_conv<NCONV, B>(n, id, k0, k1);
-            if ((self >> lane) & 1u)
-                cp = f;
-        }
-        return cp;
-    }
-
-    // the made word of the parity class of the draw the lane takes next (dw)
-    __device__ u32 made_word() const
-    {
-        if constexpr (TWO)
-            return lds_ld(mptr);
-        else
-            return lds_ld(&ctl->made[0][lane]);
-    }
-
-    // slot of the draw with counter word dw: its index mod D, times the 256
-    // bytes of a slot's word, is dw's index bits [8, 8 + log2 D) in place
-    __device__ const u32 *slot() const
-    {
-        return (const u32 *)((const char *)(ring + lane) + (dw & (u32)((D - 1) << 8)));
-    }
-
-    // the pool words of the next draw (valid where finish finds it made)
-    template <class P, int NSLOT>
-    __device__ void read(Draw<P, NSLOT> &d) const
-    {
-        lgkm_wait();   // the made word, and the previous draw's ring words, are in
-        lds_st(&ctl->done[lane], dw);
-        DrawIO<P, NSLOT>::template load_pool<D * 64>(slot(), d);
-    }
-
-    // the conversion words of the next draw's slot, loaded with its pool words
-    // (models whose conversions round stochastically): in registers by the
-    // time an event on the conversion path needs them
-    template <int NCONV, int B, int OFF>
-    __device__ void read_conv(ConvPool<NCONV, B> &cp) const
-    {
-#pragma unroll
-        for (int q = 0; q < ConvPool<NCONV, B>::NSTREAM * 4; ++q)
-            cp.w[q] = slot()[(OFF + q) * D * 64];
-    }
-
-    // its L and u2, loaded once this event's are no longer needed
-    template <class P, int NSLOT>
-    __device__ void read_tail(Draw<P, NSLOT> &d) const
-    {
-        DrawIO<P, NSLOT>::template load_tail<D * 64>(slot(), d);
-    }
-
-    // lanes whose next draw the ring does not hold (the event loop forms it
-    // itself). With x = made - (dw + 256), the draw is made (want < made <=
-    // want + D, epochs equal) exactly when x rotated right by 8 is below D:
-    // equal epochs leave a zero low byte and the index difference minus one
-    // above it; any other epoch puts a nonzero byte on top after the rotation
-    __device__ u64 miss_lanes(u32 mw, u64 act) const
-    {
-        const u32 next = dw + 256u;
-        const bool hit = __builtin_amdgcn_alignbit(mw - next, mw - next, 8) < (u32)D;
-        return act & ~lanes(hit);
-    }
-
-    // form draw `want` for the lanes in miss (the ring did not hold it)
-    template <class P, int NSLOT, int SLOT_LOG>
-    __device__ void self_draw(Draw<P, NSLOT> &d, u64 miss, u64 want, u32 id, u32 k0, u32 k1) const
-    {
-        const Draw<P, NSLOT> s = make_draw<P, NSLOT, SLOT_LOG>(want, id, k0, k1);
-        if ((miss >> lane) & 1u)
-            d = s;
-    }
-
-    // step to the draw after the next one
-    __device__ void advance()
-    {
-        dw += 256u;
-        if constexpr (TWO)
-            mptr = (const u32 *)((const char *)&ctl->made[0][lane] + (dw & 0x100u));
-    }
-};
-
-// Producer wave of one item: for each lane, the draws of its consumer lane's
-// trajectory from the claim's event index + 1 on, up to D ahead of the
-// consumer. A batch starts once some lane has START free slots; its BATCH
-// draws are formed in one block, so their Philox and logarithm chains overlap
-// (a lane with fewer free slots stores only those). The shape is measured:
-// with the event loop and this wave sharing a SIMD, 6 draws from 6 free slots
-// of 16 keep the ring ahead for binary32 and 16-bit draws, 8 from 4 for binary64.
-// STRIDE 2: one of two producers of the consumer, making the draws whose event
-// index has parity cls (PLACE_TWO0); each then holds at most D / 2 draws of
-// the ring, and a batch of 4 from 4 free places keeps its half ahead.
-// Returns once the consumer has moved past item `seq`.
-template <class P, class Md, int D, int NWMAX, int STRIDE>
-__device__ void produce_item(const LaunchArgs &L, const ItemArgs &I, RingCtl *ctl, u32 *ring, u32 seq, u32 cls)
-{
-    typedef Slots<P, Md> S;
-    typedef DrawIO<P, S::NSLOT> IO;
-    typedef ConvRing<P, Md> CR;
-    static_assert(!CR::ON || IO::NP >= 3, "the conversion mark lives in the third pool word");
-    static_assert(STRIDE == 1 || (STRIDE == 2 && D >= 4), "two producers share a ring of at least 4 slots");
-    constexpr int BATCH = STRIDE == 2 ? (D >= 16 ? 4 : D / 4) : D >= 16 ? (P::WIDE ? 8 : 6) : (D >= 2 ? D / 2 : 1);
-    constexpr int START = STRIDE == 2 ? BATCH : P::WIDE && BATCH > 4 ? 4 : BATCH;
-    const u32 lane = lane_id();
-    u32 e = 0, id = 0;
-    u64 p = 0;
-    // the loop on a 64-byte boundary, as the event loops: with its first block
-    // 4 bytes past a 32-byte boundary (where the code before it happened to
-    // leave it) the heavy trajectories' producer fell behind and the open
-    // dimerisation sweep took 457-464 ms against 414-428 aligned, every other
-    // instruction the same
-    __asm__ volatile(".p2align 6");
-    for (;;) {
-        const u32 re = lds_ld(&ctl->req_e[lane]);
-        lgkm_wait();   // a new epoch's request words were written before it
-        const u32 item = __builtin_amdgcn_readfirstlane(lds_ld(&ctl->item));
-        const u32 dw = lds_ld(&ctl->done[lane]);
-        u32 cw = 0u;
-        if constexpr (CR::ON)
-            cw = lds_ld(&ctl->convw[lane]);
-        if (item != seq)
-            break;
-        if (re != e) {
-            e = re;
-            id = lds_ld(&ctl->req_id[lane]);
-            p = (((u64)lds_ld(&ctl->req_hi[lane]) << 32) | lds_ld(&ctl->req_lo[lane])) + 1;
-            if constexpr (STRIDE == 2)
-                p += ((u32)p ^ cls) & 1u;   // the first index of this producer's parity
-        }
-        // draws made and not yet read: p - done, as a signed 24-bit difference. The
-        // event-loop lane may be ahead (it forms draws itself until the ring holds
-        // them, e.g. right after a claim): then skip to its next unread draw (of
-        // this producer's parity).
-        const bool mine = e != 0 && (dw & 0xFFu) == e;
-        i32 ahead = (i32)(((u32)p << 8) - (dw & ~0xFFu)) >> 8;
-        if (mine && ahead < 0) {
-            p += (u64)(u32)(-ahead);
-            ahead = 0;
-            if constexpr (STRIDE == 2) {
-                const u32 fix = ((u32)p ^ cls) & 1u;
-                p += fix;
-                ahead = (i32)fix;
-            }
-        }
-        // places p, p + 1, ... below done + D; this producer's draws among them
-        const u32 span = (mine && ahead < D) ? (u32)(D - ahead) : 0u;
-        const u32 room = STRIDE == 2 ? (span + 1u) >> 1 : span;
-        if (__builtin_amdgcn_ballot_w64(room >= (u32)START) == 0) {
-            __builtin_amdgcn_s_sleep(2);
-            continue;
-        }
-        Draw<P, S::NSLOT> d[BATCH];
-#pragma unroll
-        for (int b = 0; b < BATCH; ++b)
-            d[b] = make_draw<P, S::NSLOT, S::LOG>(p + (u64)(STRIDE * b), id, L.seed_lo, L.seed_hi);
-        // formed here, every one: left to the guarded stores below, each
-        // would be formed in a block of its own, one chain after another
-#pragma unroll
-        for (int b = 0; b < BATCH; ++b) {
-            __asm__ volatile("" : "+v"(d[b].L), "+v"(d[b].u2));
-            if constexpr (S::NSLOT > 0) {
-#pragma unroll
-                for (int k = 0; k < IO::NP; ++k)
-                    __asm__ volatile("" : "+v"(d[b].pool.w[k]));
-            }
-        }
-        // conversion fields of the batch, where some lane of the wave asked
-        // for them: formed for every lane, marked in each draw, stored after
-        // the draw's words
-        if constexpr (CR::ON) {
-            if (__builtin_amdgcn_ballot_w64(mine && cw != 0u) != 0) {
-                ConvPool<Md::NCONV, P::SR_B> cv[BATCH];
-#pragma unroll
-                for (int b = 0; b < BATCH; ++b)
-                    cv[b] = make_conv<Md::NCONV, P::SR_B>(p + (u64)(STRIDE * b), id, L.seed_lo, L.seed_hi);
-#pragma unroll
-                for (int b = 0; b < BATCH; ++b) {
-#pragma unroll
-                    for (int q = 0; q < CR::NW; ++q)
-                        __asm__ volatile("" : "+v"(cv[b].w[q]));
-                    d[b].pool.w[2] |= CR::MARK;
-                }
-#pragma unroll
-                for (int b = 0; b < BATCH; ++b)
-                    if ((u32)b < room) {
-                        u32 *w = ring + ((u32)(p + (u64)(STRIDE * b)) & (u32)(D - 1)) * 64 + lane;
-#pragma unroll
-                        for (int q = 0; q < CR::NW; ++q)
-                            w[(IO::NW + q) * D * 64] = cv[b].w[q];
-                    }
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < BATCH; ++b)
-            if ((u32)b < room)
-                IO::template store<D * 64>(ring + ((u32)(p + (u64)(STRIDE * b)) & (u32)(D - 1)) * 64 + lane, d[b]);
-        const u32 k = room < (u32)BATCH ? room : (u32)BATCH;
-        lgkm_wait();
-        if (k != 0u) {
-            p += (u64)(STRIDE * k);
-            lds_st(&ctl->made[STRIDE == 2 ? cls : 0u][lane], ((u32)p << 8) | e);
-        }
-    }
-    (void)I;
-}
-
-// Ring depth for draws of nw words: the largest power of two up to 16 whose
-// four rings and four control blocks fit a workgroup's LDS (gfx950: 160 KiB
-// per CU, all of it available to one workgroup; 1 KiB is left spare); 0
-// where not even a depth of 2 fits (then the 512-thread kernel runs eight
-// event-loop waves that form their own draws).
-constexpr int kLdsBytes = 160 * 1024;
-__host__ __device__ constexpr int ring_depth(int nw)
-{
-    int d = 16;
-    while (d >= 2 && 4 * d * nw * 64 * 4 + 4 * (int)sizeof(RingCtl) > kLdsBytes - 1024)
-        d /= 2;
-    return d >= 2 ? d : 0;
-}
-
-__host__ __device__ constexpr int cmax(int a, int b)
-{
-    return a > b ? a : b;
-}
-
 // --------------------------------------------------------------------------
 // Propensity versions. Each computes the same values wherever it runs; a state
 // needs one of them (wave-uniform, over the lanes holding a trajectory):
@@ -1101,8 +676,8 @@ __host__ __device__ constexpr int cmax(int a, int b)
 // long trajectory far above the exact-integer limit) takes no branch but the
 // loop's own each event. The loop test is one ballot for the states the
 // version cannot compute; a move to a cheaper version waits for the next
-// event that takes the rare path (a snapshot crossing, a fallback selection,
-// a draw the producer has not made), which costs time, never results.
+// event that takes the rare path (a snapshot crossing, a fallback selection),
+// which costs time, never results.
 // --------------------------------------------------------------------------
 enum { VER_EXACT = 0, VER_GUARD = 1, VER_CONV = 2, VER_CONV_NG = 3 };
 
@@ -1179,8 +754,8 @@ struct Versions {
 // one atomic per refill), until the counter passes E and every lane is idle.
 // Md: generated network description; P: precision policy.
 // --------------------------------------------------------------------------
-template <class P, class Md, bool PER_LANE_RATES, class F>
-__device__ void run_item(const LaunchArgs &L, const ItemArgs &I, F &feed, u32 slot_rank, u32 n_slots)
+template <class P, class Md, bool PER_LANE_RATES>
+__device__ void run_item(const LaunchArgs &L, const ItemArgs &I, u32 slot_rank, u32 n_slots)
 {
     typedef typename P::T T;
     typedef typename P::A A;
@@ -1211,11 +786,6 @@ __device__ void run_item(const LaunchArgs &L, const ItemArgs &I, F &feed, u32 sl
     Tm t_next = 0;     // time of snapshot k (infinity past the last row of this launch)
     Tm t_stop = 0;     // an event at t_new fires only if t_new <= t_stop (-infinity: suspend)
     Draw<P, NSLOT> cur = {};
-    // conversion words of cur's ring slot (RingFeed, models whose conversions
-    // round stochastically); used only where cur carries the producer's mark
-    constexpr bool CONV_RING = F::RING && ConvRing<P, Md>::ON;
-    typedef ConvPool<Md::NCONV, P::SR_B> CP;
-    CP conv_cur = {};
     u64 n_claim = 0;   // event index when this launch claimed the trajectory
     u32 rec_cnt = 0;   // recorded firings of this trajectory (Md::REC reactions)
     const u64 n_stop = L.max_events ? L.max_events : ~0ull;
@@ -1296,7 +866,6 @@ __device__ void run_item(const LaunchArgs &L, const ItemArgs &I, F &feed, u32 sl
                         t_stop = (!L.last && k >= L.k_hi) ? (Tm)(-SSA_INF_F) : t_end;
                         n_claim = n;
                         cur = make_draw<P, NSLOT, SLOT_LOG>(n, I.id_base + id, L.seed_lo, L.seed_hi);
-                        feed.claim(I.id_base + id, n);
                     }
                 }
                 if (base + cnt >= I.E)
@@ -1323,15 +892,9 @@ __device__ void run_item(const LaunchArgs &L, const ItemArgs &I, F &feed, u32 sl
             // cheaper version, every lane) that make the wave choose its version again.
             auto step = [&](auto vtag) __attribute__((always_inline)) -> u64 {
                 constexpr int V = decltype(vtag)::value;
-                // ---- draws: cur belongs to event n; event n+1's is formed (or
-                // taken from the producer's ring) alongside
+                // ---- draws: cur belongs to event n; event n+1's is formed alongside
                 const u32 id = I.id_base + idx;
-                Draw<P, NSLOT> nxt;
-                u32 made_w = 0;
-                if constexpr (F::RING)
-                    made_w = feed.made_word();
-                else
-                    nxt = make_draw<P, NSLOT, SLOT_LOG>(n + 1, id, L.seed_lo, L.seed_hi);
+                const Draw<P, NSLOT> nxt = make_draw<P, NSLOT, SLOT_LOG>(n + 1, id, L.seed_lo, L.seed_hi);
                 const Pool<NSLOT, P::SR_B> &pool = cur.pool;
                 // ---- propensities (generated op sequence) in version V.
                 // Conversions of counts draw random bits only when they round:
@@ -1346,21 +909,9 @@ __device__ void run_item(const LaunchArgs &L, const ItemArgs &I, F &feed, u32 sl
                 } else if constexpr (V == VER_GUARD) {
                     Md::template propensities<P, VS::CONV, true>(x, c, hill, a, pool, NoConv());
                 } else {
-                    // conversion fields: from the producer where it formed them
-                    // (ring feed), else formed here
-                    CP cpool;
-                    if constexpr (F::RING)
-                        cpool = feed.template conv<Md::NCONV, P::SR_B>(conv_cur, cur.pool.mark(), act, n, id,
-                                                                        L.seed_lo, L.seed_hi);
-                    else
-                        cpool = make_conv<Md::NCONV, P::SR_B>(n, id, L.seed_lo, L.seed_hi);
+                    const ConvPool<Md::NCONV, P::SR_B> cpool =
+                        make_conv<Md::NCONV, P::SR_B>(n, id, L.seed_lo, L.seed_hi);
                     Md::template propensities<P, false, V == VER_CONV>(x, c, hill, a, pool, cpool);
-                }
-                CP conv_nxt;
-                if constexpr (F::RING) {
-                    feed.read(nxt);
-                    if constexpr (CONV_RING)
-                        feed.template read_conv<Md::NCONV, P::SR_B, DrawIO<P, NSLOT>::NW>(conv_nxt);
                 }
                 // ---- optional running-max normalisation (uniform 16-bit)
                 T m = (T)1;
@@ -1406,20 +957,14 @@ __device__ void run_item(const LaunchArgs &L, const ItemArgs &I, F &feed, u32 sl
                     target = P::arnd(f32_kept(cur.u2 * a0), pool.hw(SLOT_TARGET));
                 else
                     target = cur.u2 * a0;
-                if constexpr (F::RING)
-                    feed.read_tail(nxt);   // cur's L and u2 are used by now
                 int mu = 0;
 #pragma unroll
                 for (int j = 0; j < M; ++j)
                     mu += (S[j] <= target) ? 1 : 0;
                 // ---- rare work behind one wave-uniform test (out of line): snapshots
                 // strictly before t_new hold the current state; a target at or above
-                // the total selects the last reaction with a positive propensity; a
-                // next draw the producer has not made is formed here
-                u64 miss = 0;
-                if constexpr (F::RING)
-                    miss = feed.miss_lanes(made_w, act);
-                if (__builtin_expect(((ok_lanes & (lanes(t_next < t_new) | lanes(mu == M))) | miss) != 0, 0)) {
+                // the total selects the last reaction with a positive propensity
+                if (__builtin_expect((ok_lanes & (lanes(t_next < t_new) | lanes(mu == M))) != 0, 0)) {
                     __asm__ volatile("");
                     if (active && a_ok && t_next < t_new) {
                         do {
@@ -1437,10 +982,6 @@ __device__ void run_item(const LaunchArgs &L, const ItemArgs &I, F &feed, u32 sl
                         for (int j = 0; j < M; ++j)
                             last_pos = (a[j] > (T)0) ? j : last_pos;
                         mu = last_pos;
-                    }
-                    if constexpr (F::RING) {
-                        if (miss != 0)
-                            feed.template self_draw<P, NSLOT, SLOT_LOG>(nxt, miss, n + 1, id, L.seed_lo, L.seed_hi);
                     }
                     // a cheaper version may serve the state now: leave after this event
                     // and choose again (a state V cannot compute is caught after the update)
@@ -1463,11 +1004,7 @@ __device__ void run_item(const LaunchArgs &L, const ItemArgs &I, F &feed, u32 sl
                         ++rec_cnt;
                     }
                 }
-                if constexpr (F::RING)
-                    feed.advance();
                 cur = nxt;   // a lane that stops here draws afresh when it claims again
-                if constexpr (CONV_RING)
-                    conv_cur = conv_nxt;
                 stop_lanes = act & (~fire_lanes | lanes(n == n_stop));
                 return VS::template must_leave<V>(x, act) | cheaper;
             };
@@ -1478,8 +1015,6 @@ __device__ void run_item(const LaunchArgs &L, const ItemArgs &I, F &feed, u32 sl
             int ver = VS::of(x, act);
             for (;;) {
                 u64 leave;
-                if constexpr (CONV_RING)
-                    feed.request_conv(ver >= VER_CONV ? 1u : 0u);
                 if (ver == VER_EXACT) {
                     __asm__ volatile(".p2align 6");
                     do {
@@ -1555,6 +1090,1173 @@ __device__ void run_item(const LaunchArgs &L, const ItemArgs &I, F &feed, u32 sl
             if (open || act == 0)
                 break;
         }
+    }
+}
+
+// --------------------------------------------------------------------------
+// Pipelined event loop (ssa_kernel_pl): one chain of events for 64
+// trajectories per workgroup, its work divided among the workgroup's eight
+// waves by what each part depends on.
+//
+//   event wave   propensities, partial sums, selection, integer update: the
+//                only work whose result the next event waits for
+//   clock wave   waiting times, clock, event records, the end of a trajectory and
+//                the claim of the next one: it follows the event wave, which runs
+//                ahead of it
+//   row wave     snapshot rows: it follows the clock wave
+//   draw waves   the random words, -ln(u1), u2 and conversion fields
+//
+// The waves pass batches of B events through an LDS ring of nb batches. Every
+// lane takes one event per step, so a batch is wave-uniform: event e of batch
+// b of a lane is event off + b B + e of its trajectory, and one counter per
+// wave says how far it is:
+//   next         batches handed to draw waves (each takes the next one)
+//   ready[slot]  (batch + 1) << 2 | lanes restart << 1 | conversion fields made:
+//                the batch's draws are in place
+//   done_e       batches the event wave has finished: it leaves the totals a0,
+//                the states or the selected reactions (and the running maximum)
+//                in the slot
+//   done_c       batches the clock wave has finished: it leaves the clock after
+//                each event (infinity where every row left takes the state before
+//                it, minus infinity past the end of a trajectory) and its lanes
+//   done_s       batches the row wave has finished: batch b may be drawn once
+//                b < done_s + nb, so a slot is free before it is written again
+// Nothing the event wave does depends on the clock: past the end of a trajectory
+// it computes events that nobody reads. The clock wave then claims the next
+// trajectory for the lane, writes its id, off and state to the tables and posts
+// {gen, sw}: from batch sw = done_c + nb on, the first one no draw wave can have
+// started, the lane belongs to it. A draw wave takes the tables whenever gen has
+// moved (what it draws for a lane between its two trajectories is not read), the
+// event and row waves at batch sw, which the draw and clock waves mark. The next
+// restart is posted once the row wave has finished batch sw.
+// Every wait is for a counter of a wave that does not wait for the waiting one;
+// `leave` ends all waits when the item has no trajectory left.
+// --------------------------------------------------------------------------
+typedef u32 v4u __attribute__((ext_vector_type(4)));
+typedef u32 v2u __attribute__((ext_vector_type(2)));
+
+constexpr int kPipeBatches = 16;   // most batches of a ring
+constexpr int kSnapTable = 512;    // snapshot times kept in LDS
+constexpr int kPipeLds = 150 * 1024;       // ring and tables with a CU to one workgroup
+constexpr int kPipeLdsHalf = 75 * 1024;    // with two workgroups to a CU
+
+struct __attribute__((aligned(16))) PipeCtl {
+    u32 ready[kPipeBatches];
+    u32 lanes[4 * kPipeBatches];   // clock to row wave: {lanes, restart} of a batch
+    u32 done_e, done_c, done_s, next;
+    u32 gen, convw, sw, leave;
+    u32 rmask[2];   // lanes that start a trajectory at batch sw
+    u32 live[2];    // lanes that hold one from batch sw on
+};
+
+// Words that NW words of a lane take in LDS: 16-byte units [unit][lane], then the
+// rest as 4- or 8-byte units (three words take a 16-byte unit).
+__host__ __device__ constexpr int lds_words(int nw)
+{
+    return nw + (nw % 4 == 3 ? 1 : 0);
+}
+
+// words of `streams` generator calls that hold n fields of b bits at most f a call
+__host__ __device__ constexpr int field_words(int n, int b, int f)
+{
+    return n <= 0 ? 0 : 4 * ((n - 1) / f) + (((n - 1) % f + 1) * b + 31) / 32;
+}
+
+// A slot's layout (PipeGeom::O_*, in words). First the events' pool words and u2
+// (or u2 alone), read by the event wave only; its results take the same place: a0,
+// the running maximum, then the states before each event (STATES) or the state
+// before the batch and the selected reactions. After them L, the clock wave's
+// rounding fields and the conversion words. After the ring's slots: the tables of
+// a restart (T_*).
+template <class P, class Md, bool HALF>
+struct PipeGeom {
+    typedef Slots<P, Md> S;
+    static constexpr int NA = (int)(sizeof(typename P::A) / 4);
+    static constexpr int NSLOT = S::NSLOT;
+    static constexpr bool POOL = NSLOT > 0;
+    static constexpr bool CONV = P::SR && !P::SELECTIVE && Md::NCONV > 0;
+    // pool words that hold fields (80 bits of stream 0, then whole streams)
+    static constexpr int F0 = 80 / P::SR_B, F1 = 128 / P::SR_B;
+    static constexpr int NPW = !POOL ? 0 : 3 + field_words(NSLOT - F0, P::SR_B, F1);
+    static constexpr int EW = NPW + 1;                                                     // with u2 (POOL)
+    static constexpr int CW = CONV ? field_words(Md::NCONV, P::SR_B, F1) : 0;
+    // rounding fields of the clock: waiting time, its quotient by the maximum, the
+    // clock; two to a word
+    static constexpr int NF = P::UNI && POOL ? (P::SELECTIVE ? 1 : P::NORM ? 3 : 2) : 0;
+    static constexpr int FW = (NF + 1) / 2;
+    // few species: the event wave stores every state (one LDS instruction per four
+    // events and species) and needs no reaction index; more, or an event record:
+    // it stores the reactions and the clock wave replays them where it must
+    static constexpr bool STATES = Md::N <= 3 && Md::REC == 0;
+    static constexpr int mu_bits()
+    {
+        int w = 1;
+        while ((1 << w) <= Md::M)
+            ++w;
+        return w;
+    }
+    static constexpr int MUB = mu_bits();
+    static constexpr int MUPER = 32 / MUB;   // selected reactions per word
+    static constexpr int mu_words(int b) { return (b + MUPER - 1) / MUPER; }
+    static constexpr int draw_words(int b) { return POOL ? b * lds_words(EW) : lds_words(b * NA); }
+    static constexpr int result_words(int b)
+    {
+        return lds_words(b * NA) + (P::NORM ? lds_words(b) : 0) +
+               (STATES ? Md::N * lds_words(b) : Md::N + mu_words(b));
+    }
+    static constexpr int front_words(int b)
+    {
+        return draw_words(b) > result_words(b) ? draw_words(b) : result_words(b);
+    }
+    static constexpr int slot_words(int b)
+    {
+        return 64 * (front_words(b) + lds_words(b * NA) + lds_words(b * FW) + b * lds_words(CW));
+    }
+    static constexpr int TABLE = 64 * (6 + Md::N + Md::M * NA);
+    static constexpr bool fits(int b, int n, int bytes) { return 4 * (n * slot_words(b) + TABLE) <= bytes; }
+    // Batch length B: what a wave does once a batch is shared by B events, and the
+    // event wave's straight-line code is that long. One workgroup to a CU (!HALF): the
+    // longest that leaves a ring of five batches. Two to a CU (HALF): four at most,
+    // so that eight fit and the draw waves keep several in hand.
+    static constexpr int pick()
+    {
+        for (int b = HALF ? 4 : Md::M <= 12 ? 8 : Md::M <= 32 ? 4 : 2; b >= 2; b /= 2)
+            if (fits(b, HALF ? 6 : 5, HALF ? kPipeLdsHalf : kPipeLds))
+                return b;
+        return fits(2, 4, HALF ? kPipeLdsHalf : kPipeLds) ? 2 : 0;
+    }
+    static constexpr bool OK = pick() != 0;
+    static constexpr int B = OK ? pick() : 2;
+    static constexpr int MUW = mu_words(B);
+    static constexpr int SLOT = slot_words(B);
+    static constexpr int O_EV = 0, EVS = 64 * lds_words(EW);   // one event's words to the next
+    static constexpr int O_A = 0;
+    static constexpr int O_M = O_A + 64 * lds_words(B * NA);
+    static constexpr int O_X = O_M + (P::NORM ? 64 * lds_words(B) : 0);
+    static constexpr int XS = 64 * lds_words(B);               // one species' states to the next
+    static constexpr int O_MU = O_X + 64 * Md::N;              // (!STATES)
+    static constexpr int O_L = 64 * front_words(B);
+    static constexpr int O_F = O_L + 64 * lds_words(B * NA);
+    static constexpr int O_CV = O_F + 64 * lds_words(B * FW), CVS = 64 * lds_words(CW);
+    static constexpr int T_ID = 0, T_LO = 64, T_HI = 128, T_M = 192, T_K = 256, T_IDX = 320, T_X = 384;
+    static constexpr int T_C = T_X + 64 * Md::N;
+    __device__ static u32 batches(u32 words)   // of a ring in an LDS array of so many words
+    {
+        const u32 n = (words - (u32)TABLE) / (u32)SLOT;
+        return n < (u32)kPipeBatches ? n : (u32)kPipeBatches;
+    }
+};
+
+// what the waves of a workgroup share for one item
+struct PipeWg {
+    PipeCtl *ctl;
+    u32 *ring;      // nb slots
+    u32 *tab;       // per-lane tables
+    u32 nb;         // batches of the ring
+    const u32 *snap_t;   // the first kSnapTable snapshot times of this launch's rows
+};
+
+// NW words of a lane in the layout of lds_words: consecutive lanes on consecutive
+// banks, one LDS instruction per four words
+template <int NW>
+__device__ __forceinline__ void put_words(u32 *p, u32 lane, const u32 *w)
+{
+#pragma unroll
+    for (int q = 0; q < NW / 4; ++q)
+        *(v4u *)(p + 256 * q + 4 * lane) = (v4u){w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]};
+    constexpr int r = NW % 4, q = NW / 4;
+    if constexpr (r == 1)
+        p[256 * q + lane] = w[4 * q];
+    else if constexpr (r == 2)
+        *(v2u *)(p + 256 * q + 2 * lane) = (v2u){w[4 * q], w[4 * q + 1]};
+    else if constexpr (r == 3)
+        *(v4u *)(p + 256 * q + 4 * lane) = (v4u){w[4 * q], w[4 * q + 1], w[4 * q + 2], 0u};
+}
+
+template <int NW>
+__device__ __forceinline__ void get_words(const u32 *p, u32 lane, u32 *w)
+{
+#pragma unroll
+    for (int q = 0; q < (NW + 1) / 4; ++q) {
+        const v4u v = *(const v4u *)(p + 256 * q + 4 * lane);
+        w[4 * q] = v.x;
+        w[4 * q + 1] = v.y;
+        w[4 * q + 2] = v.z;
+        if (4 * q + 3 < NW)
+            w[4 * q + 3] = v.w;
+    }
+    constexpr int r = NW % 4, q = NW / 4;
+    if constexpr (r == 1) {
+        w[4 * q] = p[256 * q + lane];
+    } else if constexpr (r == 2) {
+        const v2u v = *(const v2u *)(p + 256 * q + 2 * lane);
+        w[4 * q] = v.x;
+        w[4 * q + 1] = v.y;
+    }
+}
+
+template <class A>
+__device__ __forceinline__ A value_at(const u32 *w, int i)
+{
+    if constexpr (sizeof(A) == 4)
+        return __builtin_bit_cast(A, w[i]);
+    else
+        return __builtin_bit_cast(A, ((u64)w[2 * i + 1] << 32) | (u64)w[2 * i]);
+}
+
+template <class A>
+__device__ __forceinline__ void value_to(u32 *w, int i, A v)
+{
+    if constexpr (sizeof(A) == 4) {
+        w[i] = __builtin_bit_cast(u32, v);
+    } else {
+        const u64 b = __builtin_bit_cast(u64, v);
+        w[2 * i] = (u32)b;
+        w[2 * i + 1] = (u32)(b >> 32);
+    }
+}
+
+// a0 in (0, largest finite]
+template <class P>
+__device__ __forceinline__ bool total_ok(typename P::A a0)
+{
+    if constexpr (P::WIDE)   // positive finite binary64: bit patterns 1 .. 0x7FEFFFFFFFFFFFFF
+        return (u64)__double_as_longlong(a0) - 1ull < 0x7FEFFFFFFFFFFFFFull;
+    else
+        return __float_as_uint(a0) - 1u < 0x7F7FFFFFu;
+}
+
+// Whether the clock's short division gives the IEEE quotient for the total a0
+// (and the total can fire): its exponent is in [-500, 500) (binary64), [-60, 60)
+// (binary32), where the compiler's division sequence scales neither operand and
+// its fix-up changes nothing. -ln(u1) is 0 or in [2^-53, 37], [2^-24, 17].
+template <class P>
+__device__ __forceinline__ bool total_mid(typename P::A a0)
+{
+    if constexpr (P::WIDE)
+        return (u32)((u64)__double_as_longlong(a0) >> 32) - 0x20B00000u < 0x3E800000u;
+    else
+        return __float_as_uint(a0) - 0x21800000u < 0x3C000000u;
+}
+
+template <class P>
+__device__ __forceinline__ typename P::A wait_mid(typename P::A l, typename P::A a0)
+{
+    if constexpr (P::WIDE)
+        return div_rn_log64(l, a0);
+    else if constexpr (P::NARROW && P::UNI)
+        return P::tau_div(l, a0);
+    else
+        return div_rn_inrange(l, a0);
+}
+
+// every LDS access before it has completed, none after it has started
+__device__ __forceinline__ void lds_fence()
+{
+    __asm__ volatile("" ::: "memory");
+    lgkm_wait();
+}
+
+// c ? a : b as one select of its own: left to itself the compiler folds a tree of
+// selects of +-1 into flags, a comparison and one more select
+__device__ __forceinline__ i32 pick(bool c, i32 a, i32 b)
+{
+    i32 v = c ? a : b;
+    __asm__("" : "+v"(v));
+    return v;
+}
+
+// whether this lane is in the mask
+__device__ __forceinline__ bool in_mask(u64 m)
+{
+    return __builtin_amdgcn_inverse_ballot_w64(m);
+}
+
+// a uniform LDS word
+__device__ __forceinline__ u32 ctl_ld(const u32 *p)
+{
+    return (u32)__builtin_amdgcn_readfirstlane(lds_ld(p));
+}
+
+// ------------------------------------------------------------ draw waves
+template <class P, class Md, bool HALF>
+__device__ void pipe_draw(const LaunchArgs &L, const PipeWg &W)
+{
+    typedef PipeGeom<P, Md, HALF> G;
+    typedef Slots<P, Md> S;
+    typedef typename P::A A;
+    constexpr int B = G::B, NA = G::NA;
+    constexpr int GR = B < 4 ? B : 4;   // draws formed together: their chains overlap
+    const u32 lane = lane_id();
+    PipeCtl *ctl = W.ctl;
+    u32 gen = 0, id = 0, si = 0, sw = 0;
+    u64 off = 0, b64 = 0;
+    for (;;) {
+        u32 nb = 0;
+        if (lane == 0)
+            nb = __hip_atomic_fetch_add(&ctl->next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const u32 b = (u32)__builtin_amdgcn_readfirstlane(nb);
+        const u32 step = b - (u32)b64;
+        b64 += (u64)step;
+        si += step;
+        while (si >= W.nb)   // b mod nb
+            si -= W.nb;
+        for (;;) {
+            const u32 dc = lds_ld(&ctl->done_s), lv = lds_ld(&ctl->leave);
+            if ((u32)__builtin_amdgcn_readfirstlane(lv) != 0u)
+                return;
+            if ((i32)(b - (u32)__builtin_amdgcn_readfirstlane(dc)) < (i32)W.nb)
+                break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        lds_fence();   // the restart of a batch is posted before the count that frees its slot
+        const u32 g = ctl_ld(&ctl->gen);
+        const bool conv = G::CONV && ctl_ld(&ctl->convw) != 0u;
+        lds_fence();
+        if (g != gen) {
+            gen = g;
+            sw = ctl_ld(&ctl->sw);
+            id = W.tab[G::T_ID + lane];
+            off = ((u64)W.tab[G::T_HI + lane] << 32) | W.tab[G::T_LO + lane];
+        }
+        u32 *slot = W.ring + si * G::SLOT;
+        const u64 n0 = off + b64 * B;
+#pragma unroll
+        for (int e0 = 0; e0 < B; e0 += GR) {
+            Draw<P, S::NSLOT> d[GR];
+#pragma unroll
+            for (int e = 0; e < GR; ++e)
+                d[e] = make_draw<P, S::NSLOT, S::LOG>(n0 + (u64)(e0 + e), id, L.seed_lo, L.seed_hi);
+            u32 lw[GR * NA], uw[GR * NA];
+#pragma unroll
+            for (int e = 0; e < GR; ++e) {
+                value_to<A>(lw, e, d[e].L);
+                value_to<A>(uw, e, d[e].u2);
+            }
+            put_words<GR * NA>(slot + G::O_L + 64 * e0 * NA, lane, lw);
+            if constexpr (G::POOL) {
+#pragma unroll
+                for (int e = 0; e < GR; ++e) {
+                    u32 w[G::EW];
+#pragma unroll
+                    for (int k = 0; k < G::NPW; ++k)
+                        w[k] = d[e].pool.w[k];
+                    w[G::NPW] = uw[e];
+                    put_words<G::EW>(slot + G::O_EV + G::EVS * (e0 + e), lane, w);
+                }
+                if constexpr (G::NF > 0) {
+                    u32 fw[GR * G::FW];
+#pragma unroll
+                    for (int e = 0; e < GR; ++e) {
+                        const u32 time = d[e].pool.hw(S::TIME);
+                        if constexpr (G::NF == 1) {
+                            fw[e] = time;
+                        } else {
+                            fw[e * G::FW] = (time & 0xFFFF0000u) | (d[e].pool.hw(S::TAU) >> 16);
+                            if constexpr (G::NF == 3)
+                                fw[e * G::FW + 1] = d[e].pool.hw(S::TAUM);
+                        }
+                    }
+                    put_words<GR * G::FW>(slot + G::O_F + 64 * e0 * G::FW, lane, fw);
+                }
+            } else {
+                put_words<GR * NA>(slot + G::O_EV + 64 * e0 * NA, lane, uw);
+            }
+        }
+        if constexpr (G::CONV) {
+            if (conv) {
+#pragma unroll
+                for (int e = 0; e < B; ++e) {
+                    const ConvPool<Md::NCONV, P::SR_B> cv =
+                        make_conv<Md::NCONV, P::SR_B>(n0 + (u64)e, id, L.seed_lo, L.seed_hi);
+                    put_words<G::CW>(slot + G::O_CV + G::CVS * e, lane, cv.w);
+                }
+            }
+        }
+        lds_fence();
+        lds_st(ctl->ready + si, (b + 1u) << 2 | (b == sw ? 2u : 0u) | (conv ? 1u : 0u));
+    }
+}
+
+// ------------------------------------------------------------ event wave
+template <class P, class Md, bool HALF, bool PER_LANE_RATES>
+__device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg &W)
+{
+    typedef typename P::T T;
+    typedef typename P::A A;
+    typedef Slots<P, Md> S;
+    typedef PipeGeom<P, Md, HALF> G;
+    constexpr int N = Md::N, M = Md::M, B = G::B, NA = G::NA;
+    constexpr int FW = G::POOL ? G::EW : B * NA;   // words loaded as a batch starts
+    typedef ConvPool<Md::NCONV, P::SR_B> CP;
+    const u32 lane = lane_id();
+    PipeCtl *ctl = W.ctl;
+
+    const T *rates = (const T *)I.rates;
+    T hill[2 * M];
+#pragma unroll
+    for (int j = 0; j < 2 * M; ++j)
+        hill[j] = uniform_value(((const T *)I.hill)[j]);
+    i32 x[N] = {};
+    T c[M] = {};
+    if constexpr (!PER_LANE_RATES) {
+#pragma unroll
+        for (int j = 0; j < M; ++j)
+            c[j] = uniform_value(rates[j]);
+    }
+    float mrun = 0.0f;
+    u32 convw = 0, tag = 0;
+    u64 live = 0;
+    bool more = true;
+    u64 over = 0;    // all lanes once the item has ended
+
+    // Waits until batch b (slot `at`) is drawn; r: its ready word as read earlier. Once
+    // the item has ended, `more` is false.
+    auto acquire = [&](u32 b, u32 at, u32 r) __attribute__((always_inline)) {
+        u32 v = (u32)__builtin_amdgcn_readfirstlane(r);
+        if (__builtin_expect((v >> 2) != ((b + 1u) & 0x3FFFFFFFu), 0)) {
+            for (;;) {
+                const u32 r1 = lds_ld(ctl->ready + at), lv = lds_ld(&ctl->leave);
+                v = (u32)__builtin_amdgcn_readfirstlane(r1);
+                if ((v >> 2) == ((b + 1u) & 0x3FFFFFFFu))
+                    break;
+                if ((u32)__builtin_amdgcn_readfirstlane(lv) != 0u) {
+                    more = false;   // (left by the rare branch after the batch)
+                    over = ~0ull;
+                    break;
+                }
+            }
+        }
+        tag = v;
+        __asm__ volatile("" ::: "memory");
+    };
+
+    acquire(0u, 0u, 0u);
+    if (!more)
+        return;
+    u32 si_next = 0;
+    __asm__ volatile(".p2align 6");
+    for (u32 b = 0;; ++b) {
+        const u32 si = (u32)__builtin_amdgcn_readfirstlane(si_next);   // b mod nb
+        u32 *slot = W.ring + si * G::SLOT;
+        u32 first[FW];   // event 0's words, or every u2: in flight while the batch is looked over
+        get_words<FW>(slot + G::O_EV, lane, first);
+        if (__builtin_expect((tag & 2u) != 0u, 0)) {   // lanes take their next trajectory
+            const u64 rm = ((u64)ctl_ld(&ctl->rmask[1]) << 32) | ctl_ld(&ctl->rmask[0]);
+            live = ((u64)ctl_ld(&ctl->live[1]) << 32) | ctl_ld(&ctl->live[0]);
+            if ((rm >> lane) & 1u) {
+#pragma unroll
+                for (int s = 0; s < N; ++s)
+                    x[s] = (i32)W.tab[G::T_X + 64 * s + lane];
+                mrun = __uint_as_float(W.tab[G::T_M + lane]);
+                if constexpr (PER_LANE_RATES) {
+#pragma unroll
+                    for (int j = 0; j < M; ++j) {
+                        u32 w[NA];
+#pragma unroll
+                        for (int k = 0; k < NA; ++k)
+                            w[k] = W.tab[G::T_C + 64 * (j * NA + k) + lane];
+                        c[j] = (T)value_at<A>(w, 0);
+                    }
+                }
+            }
+            lds_fence();   // waited for in here, not by every batch
+        }
+        i32 x0[N];
+#pragma unroll
+        for (int s = 0; s < N; ++s)
+            x0[s] = x[s];
+        const float m_start = mrun;
+        const u32 si2 = si + 1u == W.nb ? 0u : si + 1u;
+        const bool conv_made = (tag & 1u) != 0u;
+        u64 again = L.guard != 0u ? ~0ull : 0ull;   // lanes whose batch has to be computed again with every case
+        u32 aw[B * NA], mw[B], muw[G::MUW] = {}, xw[G::STATES ? N : 1][B];
+
+        // The batch in straight line. KIND 0: every count within the exact-integer
+        // limit; 1: conversions round, with the fields that came with the draws; 2:
+        // every case (zero guards, conversion fields formed here, a target at or
+        // above the total), from the state before the batch.
+        auto batch = [&](auto kind) __attribute__((always_inline)) {
+            constexpr int KIND = decltype(kind)::value;
+            __asm__ volatile("; kind %0" ::"i"(KIND));   // (keeps the kinds' common loads in each)
+            u32 uw[G::POOL ? 1 : B * NA];
+            if constexpr (!G::POOL) {
+#pragma unroll
+                for (int k = 0; k < FW; ++k)
+                    uw[k] = first[k];
+            }
+            u64 n = 0;
+            u32 id = 0;
+            if constexpr (KIND == 2) {
+#pragma unroll
+                for (int s = 0; s < N; ++s)
+                    x[s] = x0[s];
+                mrun = m_start;
+                id = W.tab[G::T_ID + lane];
+                n = (((u64)W.tab[G::T_HI + lane] << 32) | W.tab[G::T_LO + lane]) + (u64)b * B;
+#pragma unroll
+                for (int k = 0; k < G::MUW; ++k)
+                    muw[k] = 0u;
+            }
+            u32 r2 = 0;
+            u32 ew[G::POOL ? G::EW : 1];   // the next event's words, loaded while this one runs
+            if constexpr (G::POOL) {
+#pragma unroll
+                for (int k = 0; k < FW; ++k)
+                    ew[k] = first[k];
+            }
+#pragma unroll
+            for (int e = 0; e < B; ++e) {
+                Pool<S::NSLOT, P::SR_B> pool;
+                A u2;
+                if constexpr (G::POOL) {
+#pragma unroll
+                    for (int k = 0; k < G::NPW; ++k)
+                        pool.w[k] = ew[k];
+                    u2 = value_at<A>(ew, G::NPW);
+                    if (e + 1 < B)
+                        get_words<G::EW>(slot + G::O_EV + G::EVS * (e + 1), lane, ew);
+                } else {
+                    u2 = value_at<A>(uw, e);
+                }
+                if (KIND != 2 && e == B / 2) {
+                    // the last batch's words have long been written: publish it, and ask
+                    // for the next one's state
+                    __asm__ volatile("" : "+v"(x[0]));   // not before this event
+                    lds_fence();
+                    lds_st(&ctl->done_e, b);
+                    r2 = lds_ld(ctl->ready + si2);
+                }
+                if (KIND != 2 && e == B - 1) {
+                    __asm__ volatile("" : "+v"(r2), "+v"(x[0]));   // not before this event
+                    acquire(b + 1u, si2, r2);
+                }
+                if constexpr (G::STATES) {
+#pragma unroll
+                    for (int s = 0; s < N; ++s)
+                        xw[s][e] = (u32)x[s];
+                }
+                T a[M];
+                if constexpr (G::CONV && KIND == 2) {
+                    const CP cp = make_conv<Md::NCONV, P::SR_B>(n + (u64)e, id, L.seed_lo, L.seed_hi);
+                    Md::template propensities<P, false, true>(x, c, hill, a, pool, cp);
+                } else if constexpr (KIND == 2) {
+                    Md::template propensities<P, false, true>(x, c, hill, a, pool, NoConv());
+                } else if constexpr (KIND == 1) {
+                    CP cp;
+                    get_words<G::CW>(slot + G::O_CV + G::CVS * e, lane, cp.w);
+                    Md::template propensities<P, false, Md::template needs_guard<P>()>(x, c, hill, a, pool, cp);
+                } else {
+                    Md::template propensities<P, G::CONV, Md::template needs_guard<P>()>(x, c, hill, a, pool, NoConv());
+                }
+                if constexpr (P::NORM) {
+                    float mx = 0.0f;
+#pragma unroll
+                    for (int j = 0; j < M; ++j)
+                        mx = a[j] > mx ? a[j] : mx;
+                    mrun = mx > mrun ? mx : mrun;
+                    mw[e] = __float_as_uint(mrun);
+#pragma unroll
+                    for (int j = 0; j < M; ++j)
+                        a[j] = P::div(a[j], mrun, pool.hw(S::NORM + j));
+                }
+                A sum[M];
+                sum[0] = (A)a[0];
+#pragma unroll
+                for (int j = 1; j < M; ++j)
+                    sum[j] = P::acc(sum[j - 1], a[j], pool.hw(S::SUM + j - 1));
+                const A a0 = sum[M - 1];
+                A target;
+                if constexpr (P::UNI)
+                    target = P::arnd(f32_kept(u2 * a0), pool.hw(S::TARGET));
+                else
+                    target = u2 * a0;
+                // past[j]: the reaction comes after j (partial sums never fall, so the
+                // first false one names it)
+                bool past[M];
+#pragma unroll
+                for (int j = 0; j < M; ++j)
+                    past[j] = sum[j] <= target;
+                if constexpr (KIND == 2) {
+                    int mu = 0, last_pos = 0;
+#pragma unroll
+                    for (int j = 0; j < M; ++j) {
+                        mu += past[j] ? 1 : 0;
+                        last_pos = (a[j] > (T)0) ? j : last_pos;
+                    }
+                    mu = mu == M && total_ok<P>(a0) ? last_pos : mu;
+                    Md::update(x, mu);
+                    muw[e / G::MUPER] |= (u32)mu << (G::MUB * (e % G::MUPER));
+                } else if constexpr (G::STATES) {
+                    again |= lanes(past[M - 1]);
+                    Md::advance(x, past);
+                } else {
+                    again |= lanes(past[M - 1]);
+                    const int mu = Md::reaction(past);
+                    Md::update(x, mu);
+                    muw[e / G::MUPER] |= (u32)mu << (G::MUB * (e % G::MUPER));
+                }
+                value_to<A>(aw, e, a0);
+            }
+        };
+        bool conv_now = false;
+        if constexpr (G::CONV) {
+            // counts grow by at most DMAX an event; the draw waves are asked for
+            // conversion fields some batches before one reaches the limit
+            constexpr int lim = P::EXACT_INT - (B - 1) * Md::DMAX, near = P::EXACT_INT - 96 * Md::DMAX;
+            const u32 mx = Versions<P, Md>::max_count(x);
+            const u64 close = near < 0 ? live : live & lanes(mx > (u32)near);
+            if (__builtin_expect(close != 0 || convw != 0u, 0)) {
+                const bool cv = lim < 0 ? live != 0 : (live & lanes(mx > (u32)lim)) != 0;
+                const u32 want = close != 0 ? 1u : 0u;
+                if (want != convw) {
+                    convw = want;
+                    lds_st(&ctl->convw, want);
+                }
+                if (cv && !conv_made)
+                    again = ~0ull;
+                conv_now = cv && conv_made;
+            }
+        }
+        if constexpr (G::CONV) {
+            if (conv_now)
+                batch(IC<1>());
+            else
+                batch(IC<0>());
+        } else {
+            batch(IC<0>());
+        }
+        if (__builtin_expect(((again & live) | over) != 0, 0)) {
+            if (!more)
+                return;
+            batch(IC<2>());
+        }
+        put_words<B * NA>(slot + G::O_A, lane, aw);
+        if constexpr (P::NORM)
+            put_words<B>(slot + G::O_M, lane, mw);
+        if constexpr (G::STATES) {
+#pragma unroll
+            for (int s = 0; s < N; ++s)
+                put_words<B>(slot + G::O_X + G::XS * s, lane, xw[s]);
+        } else {
+#pragma unroll
+            for (int s = 0; s < N; ++s)
+                slot[G::O_X + 64 * s + lane] = (u32)x0[s];
+#pragma unroll
+            for (int k = 0; k < G::MUW; ++k)
+                slot[G::O_MU + 64 * k + lane] = muw[k];
+        }
+        si_next = si2;
+    }
+}
+
+// ------------------------------------------------------------ clock wave
+template <class P, class Md, bool HALF, bool PER_LANE_RATES>
+__device__ void pipe_clock(const LaunchArgs &L, const ItemArgs &I, const PipeWg &W)
+{
+    typedef typename P::T T;
+    typedef typename P::A A;
+    typedef typename P::Tm Tm;
+    typedef Slots<P, Md> S;
+    typedef PipeGeom<P, Md, HALF> G;
+    constexpr int N = Md::N, M = Md::M, B = G::B, NA = G::NA;
+    const u32 lane = lane_id();
+    PipeCtl *ctl = W.ctl;
+    const T *rates = (const T *)I.rates;
+    const Tm t_end = P::WIDE ? (Tm)L.t_end64 : (Tm)L.t_end32;
+    const u64 n_stop = L.max_events ? L.max_events : ~0ull;
+    Tm t = 0, t_lim = 0;   // an event at t_new fires only if t_new <= t_lim
+    Tm t_hold = 0;         // clock of a trajectory whose first batch is still to come
+    u64 off = 0;           // event e of batch b is event off + b B + e
+    u64 cap_b = 0;         // batches from here on hold the event cap
+    u64 n_claim = 0;
+    u32 idx = 0, rec_cnt = 0, gen = 0, sw = 0;
+    u64 act = 0, hold = 0;   // lanes in a trajectory, lanes waiting for batch sw
+    bool open = true, pending = false, changed = false;
+    // past the last row of this launch a trajectory is suspended (the last launch: ends)
+    const Tm t_rows = L.last ? t_end : L.k_hi > L.k_lo ? snap_time<P>(L, L.k_hi - 1) : (Tm)(-SSA_INF_F);
+
+    // trajectories for the lanes without one; their first batch is at_batch
+    auto claim = [&](u64 at_batch) {
+        u64 fresh = 0;
+        while (open) {
+            const u64 need = ~(act | hold);
+            if (need == 0)
+                break;
+            const u32 cnt = (u32)__popcll(need);
+            const u32 leader = (u32)__ffsll((long long)need) - 1u;
+            u32 base = 0;
+            if (lane == leader)
+                base = atomicAdd(I.counter, cnt);
+            base = __builtin_amdgcn_readlane(base, leader);
+            bool run = false;
+            if (in_mask(need)) {
+                const u32 w = base + rank_in(need);
+                if (w < I.E) {
+                    const u32 id = I.order ? I.order[w] : w;
+                    i32 x[N];
+                    float mrun = 0.0f;
+                    i32 k = 0;
+                    run = true;
+                    t_hold = 0;
+                    n_claim = 0;
+                    rec_cnt = 0;
+                    if (L.first) {
+#pragma unroll
+                        for (int s = 0; s < N; ++s)
+                            x[s] = I.x0[s];
+                    } else {
+#pragma unroll
+                        for (int s = 0; s < N; ++s)
+                            x[s] = I.cx[(u64)s * I.E + id];
+                        t_hold = (Tm)I.ct[id];
+                        n_claim = I.cn[id];
+                        k = I.ck[id];
+                        mrun = I.cm[id];
+                        if constexpr (Md::REC != 0)
+                            rec_cnt = I.rec_n[id];
+                        if (I.status[id] != ST_SUSPENDED) {
+                            if (I.work)
+                                I.work[id] = 0u;
+                            // finished in an earlier chunk: fill this chunk's rows
+                            for (int kk = L.k_lo; kk < L.k_hi; ++kk)
+#pragma unroll
+                                for (int s = 0; s < N; ++s)
+                                    I.snap[((u64)(kk - L.k_lo) * N + s) * I.E + id] = x[s];
+                            run = false;
+                        }
+                    }
+                    if (run) {
+                        idx = id;
+                        t_lim = !L.last && k >= L.k_hi ? (Tm)(-SSA_INF_F) : t_rows;
+                        off = n_claim - at_batch * B;
+                        cap_b = at_batch + (n_stop - n_claim) / (u64)B;
+                        W.tab[G::T_K + lane] = (u32)k;
+                        W.tab[G::T_IDX + lane] = id;
+                        W.tab[G::T_ID + lane] = I.id_base + id;
+                        W.tab[G::T_LO + lane] = (u32)off;
+                        W.tab[G::T_HI + lane] = (u32)(off >> 32);
+                        W.tab[G::T_M + lane] = __float_as_uint(mrun);
+#pragma unroll
+                        for (int s = 0; s < N; ++s)
+                            W.tab[G::T_X + 64 * s + lane] = (u32)x[s];
+                        if constexpr (PER_LANE_RATES) {
+                            const u32 set = I.traj_per_set ? id / I.traj_per_set : 0u;
+#pragma unroll
+                            for (int j = 0; j < M; ++j) {
+                                u32 w2[NA];
+                                value_to<A>(w2, 0, (A)rates[(u64)set * M + j]);
+#pragma unroll
+                                for (int q = 0; q < NA; ++q)
+                                    W.tab[G::T_C + 64 * (j * NA + q) + lane] = w2[q];
+                            }
+                        }
+                    }
+                }
+            }
+            fresh |= lanes(run);
+            hold |= lanes(run);
+            if (base + cnt >= I.E)
+                open = false;
+        }
+        sw = (u32)at_batch;
+        gen += 1u;
+        lds_st(&ctl->rmask[0], (u32)fresh);
+        lds_st(&ctl->rmask[1], (u32)(fresh >> 32));
+        lds_st(&ctl->live[0], (u32)(act | hold));
+        lds_st(&ctl->live[1], (u32)((act | hold) >> 32));
+        lds_st(&ctl->sw, sw);
+        lds_fence();
+        lds_st(&ctl->gen, gen);
+        lds_fence();
+        pending = true;
+        changed = false;
+    };
+
+    claim(0);
+    lds_st(&ctl->done_s, 0u);
+    u32 si_next = 0, e_done = 0;
+    u64 b = 0;
+    for (;; ++b) {
+        if ((act | hold) == 0 && !open)
+            break;   // the queue is empty and no lane runs
+        const u32 bl = (u32)b;
+        const u32 si = (u32)__builtin_amdgcn_readfirstlane(si_next);
+        u32 *slot = W.ring + si * G::SLOT;
+        if ((i32)(e_done - bl) <= 0) {
+            // the event wave is behind: what the row wave waits for goes out first
+            lds_fence();
+            lds_st(&ctl->done_c, bl);
+            for (;;) {
+                e_done = ctl_ld(&ctl->done_e);
+                if ((i32)(e_done - bl) > 0)
+                    break;
+                __builtin_amdgcn_s_sleep(1);
+            }
+            __asm__ volatile("" ::: "memory");
+        }
+        const bool restart = pending && bl == sw;
+        if (restart) {
+            t = in_mask(hold) ? t_hold : t;
+            act |= hold;
+            hold = 0;
+            pending = false;
+        }
+        // ---- the batch's clock values, as if every event fired
+        u32 lw[B * NA], aw[B * NA], mw[P::NORM ? B : 1] = {};
+        get_words<B * NA>(slot + G::O_L, lane, lw);
+        get_words<B * NA>(slot + G::O_A, lane, aw);
+        if constexpr (P::NORM)
+            get_words<B>(slot + G::O_M, lane, mw);
+        u32 fw[G::NF > 0 ? B * G::FW : 1] = {};
+        if constexpr (G::NF > 0)
+            get_words<B * G::FW>(slot + G::O_F, lane, fw);
+        const u32 e_now = lds_ld(&ctl->done_e);
+        lds_fence();   // with these words, what this wave wrote for the last batch is in place
+        lds_st(&ctl->done_c, bl);
+        e_done = (u32)__builtin_amdgcn_readfirstlane(e_now);
+        Tm tn[B];
+        u64 ok[B], mid = ~0ull;   // ok: lanes whose total (and running maximum) can fire event e
+        auto clock = [&](auto full_range) __attribute__((always_inline)) {
+            constexpr bool FULL = decltype(full_range)::value != 0;
+#pragma unroll
+            for (int e = 0; e < B; ++e) {
+                const A a0 = value_at<A>(aw, e), l = value_at<A>(lw, e);
+                const Tm before = e ? tn[e - 1] : t;
+                const A wait = FULL ? P::tau_div(l, a0) : wait_mid<P>(l, a0);
+                if constexpr (P::UNI) {
+                    // fields in the upper halfword; below it are bits no conversion reads
+                    const u32 f0 = G::NF > 0 ? fw[G::NF > 0 ? e * G::FW : 0] : 0u;
+                    A tau = P::arnd(wait, f0 << 16);
+                    if constexpr (P::NORM)
+                        tau = P::arnd(P::quotient(tau, __uint_as_float(mw[e])),
+                                      G::NF == 3 ? fw[G::NF == 3 ? e * G::FW + 1 : 0] : 0u);
+                    tn[e] = P::tacc(before + tau, f0);
+                } else {
+                    tn[e] = before + wait;
+                }
+                if constexpr (FULL) {
+                    ok[e] = lanes(total_ok<P>(a0));
+                } else {
+                    ok[e] = lanes(total_mid<P>(a0));
+                }
+                if constexpr (P::NORM)
+                    ok[e] &= lanes(__uint_as_float(mw[e]) > 0.0f) & lanes(__uint_as_float(mw[e]) <= 3.40282347e38f);
+                if constexpr (!FULL)
+                    mid &= ok[e];
+            }
+        };
+        clock(IC<0>());
+        // no lane ends or reaches the cap: the clock moves on
+        const u64 plain = mid & lanes(tn[B - 1] <= t_lim) & lanes(b < cap_b);
+        const u64 was = act;
+        const Tm t_before = t;
+        if (Md::REC != 0 || (act & ~plain) != 0) {
+            if ((act & ~mid) != 0)
+                clock(IC<1>());
+            t = tn[B - 1];
+            u64 run = act;          // lanes still in their trajectory
+            u32 stop_e = 0;         // the event a lane stops at (it does not fire)
+            Tm t_at = 0, t_over = 0;
+            A a_at = 0;
+            float m_at = 1.0f;
+            // rem: events until the cap, for lanes near it
+            const u64 n0 = off + b * (u64)B;
+            const u32 rem = b < cap_b ? (u32)B : (u32)(n_stop - n0);
+#pragma unroll
+            for (int e = 0; e < B; ++e) {
+                const Tm t_new = tn[e];
+                const u64 fire = run & ok[e] & lanes(t_new <= t_lim) & ~lanes(rem == (u32)e);
+                const u64 stop = run & ~fire;
+                if (Md::REC != 0) {
+                    const int mu = (int)((slot[G::O_MU + 64 * (e / G::MUPER) + lane] >> (G::MUB * (e % G::MUPER))) &
+                                         ((1u << G::MUB) - 1u));
+                    if (in_mask(fire) && ((Md::REC >> mu) & 1ull)) {
+                        if (rec_cnt < I.rec_cap) {
+                            I.rec_t[(u64)idx * I.rec_cap + rec_cnt] = (double)t_new;
+                            I.rec_j[(u64)idx * I.rec_cap + rec_cnt] = (unsigned char)mu;
+                        }
+                        ++rec_cnt;
+                    }
+                }
+                if (stop) {
+                    if (in_mask(stop)) {
+                        stop_e = (u32)e;
+                        t_at = e ? tn[e ? e - 1 : 0] : t_before;
+                        t_over = t_new;
+                        a_at = value_at<A>(aw, e);
+                        m_at = P::NORM ? __uint_as_float(mw[P::NORM ? e : 0]) : 1.0f;
+                    }
+                    run = fire;
+                }
+            }
+            const u64 ended = act & ~run;
+            if (in_mask(ended)) {
+                // what the row wave sees: a trajectory that stops in its state leaves it to
+                // every row from here on, and nothing follows
+                const bool frozen = rem == stop_e || !(t_over > t_lim) || !total_ok<P>(a_at) ||
+                                    (P::NORM && !(m_at > 0.0f && m_at <= 3.40282347e38f));
+#pragma unroll
+                for (int e = 0; e < B; ++e)
+                    tn[e] = (u32)e > stop_e ? (Tm)(-SSA_INF_F) : (u32)e == stop_e && frozen ? (Tm)SSA_INF_F : tn[e];
+                i32 x[N];
+                if constexpr (G::STATES) {
+#pragma unroll
+                    for (int s = 0; s < N; ++s)
+                        x[s] = (i32)slot[G::O_X + G::XS * s +
+                                         (B >= 4 ? 256 * (stop_e / 4u) + 4 * lane + stop_e % 4u : B * lane + stop_e)];
+                } else {
+#pragma unroll
+                    for (int s = 0; s < N; ++s)
+                        x[s] = (i32)slot[G::O_X + 64 * s + lane];
+#pragma unroll
+                    for (int e = 0; e < B; ++e) {
+                        const u32 mu = (slot[G::O_MU + 64 * (e / G::MUPER) + lane] >> (G::MUB * (e % G::MUPER))) &
+                                       ((1u << G::MUB) - 1u);
+                        Md::update(x, (u32)e < stop_e ? (int)mu : M);
+                    }
+                }
+                // ---- finish (or suspend) this trajectory, once per trajectory
+                const u64 n = n0 + (u64)stop_e;
+                const bool m_ok = !P::NORM || (m_at > 0.0f && m_at <= 3.40282347e38f);
+                int status;
+                if (rem == stop_e)
+                    status = ST_CAPPED;
+                else if (!m_ok)
+                    status = !(m_at <= 3.40282347e38f) ? ST_OVERFLOW : ST_ABSORBED;
+                else if (!total_ok<P>(a_at))
+                    status = !(a_at <= (P::WIDE ? (A)1.7976931348623157e308 : (A)3.40282347e38f)) ? ST_OVERFLOW
+                                                                                                  : ST_ABSORBED;
+                else
+                    status = t_over > t_end ? ST_DONE : ST_SUSPENDED;
+                if (status != ST_SUSPENDED) {
+                    I.n_events[idx] = n;
+                    I.t_last[idx] = (double)t_at;
+                }
+                I.status[idx] = (unsigned char)status;
+                if (I.work)
+                    I.work[idx] = (u32)(n - n_claim);
+                if constexpr (Md::REC != 0)
+                    I.rec_n[idx] = rec_cnt;
+                if (!L.last) {
+#pragma unroll
+                    for (int s = 0; s < N; ++s)
+                        I.cx[(u64)s * I.E + idx] = x[s];
+                    I.ct[idx] = (double)t_at;
+                    I.cn[idx] = n;
+                    I.ck[idx] = L.k_hi;
+                    I.cm[idx] = P::NORM ? m_at : 0.0f;
+                }
+            }
+            act = run;
+            changed = changed || ended != 0;
+        } else {
+            t = tn[B - 1];
+        }
+        // for the row wave, in the place of L
+        u32 tw[B * NA];
+#pragma unroll
+        for (int e = 0; e < B; ++e)
+            value_to<A>(tw, e, (A)tn[e]);
+        put_words<B * NA>(slot + G::O_L, lane, tw);
+        *(v4u *)(ctl->lanes + 4 * si) = (v4u){(u32)was, (u32)(was >> 32), restart ? 1u : 0u, 0u};
+        if (__builtin_expect(!pending && changed, 0)) {
+            if ((i32)(ctl_ld(&ctl->done_s) - sw) > 0)
+                claim(b + W.nb);
+        }
+        si_next = si + 1u == W.nb ? 0u : si + 1u;
+    }
+    lds_fence();
+    lds_st(&ctl->done_c, (u32)b);
+    lds_fence();
+    lds_st(&ctl->leave, 1u);
+    lds_fence();
+}
+
+// ------------------------------------------------------------ row wave
+template <class P, class Md, bool HALF>
+__device__ void pipe_rows(const LaunchArgs &L, const ItemArgs &I, const PipeWg &W)
+{
+    typedef typename P::A A;
+    typedef typename P::Tm Tm;
+    typedef PipeGeom<P, Md, HALF> G;
+    constexpr int N = Md::N, B = G::B, NA = G::NA;
+    const u32 lane = lane_id();
+    PipeCtl *ctl = W.ctl;
+    Tm t_next = (Tm)SSA_INF_F, t_after = (Tm)SSA_INF_F;   // times of the lane's next two rows
+    i32 *row = nullptr;                                   // where the next one goes
+    i32 k = 0;
+    // time of row r: from the LDS table, which ends with two infinities; past a table
+    // that does not hold all of this launch's rows, from memory
+    const bool all_rows = L.k_hi - L.k_lo <= kSnapTable;
+    auto row_time = [&](i32 r) __attribute__((always_inline)) -> Tm {
+        const i32 i = r - L.k_lo;
+        Tm v = ((const Tm *)W.snap_t)[i <= kSnapTable ? i : kSnapTable + 1];
+        if (__builtin_expect(!all_rows, 0)) {
+            if (i >= kSnapTable)
+                v = r < L.k_hi ? snap_time<P>(L, r) : (Tm)SSA_INF_F;
+            // the wait for this load stays in here: where the paths join it would hold
+            // for every row stored before
+            __asm__ volatile("" : "+v"(v));
+        }
+        return v;
+    };
+    u32 si_next = 0, c_done = 0;
+    for (u32 b = 0;; ++b) {
+        const u32 si = (u32)__builtin_amdgcn_readfirstlane(si_next);
+        while ((i32)(c_done - b) <= 0) {
+            const u32 lv = lds_ld(&ctl->leave);
+            __asm__ volatile("" ::: "memory");
+            const u32 dc = lds_ld(&ctl->done_c);
+            c_done = (u32)__builtin_amdgcn_readfirstlane(dc);
+            if ((i32)(c_done - b) > 0)
+                break;
+            if ((u32)__builtin_amdgcn_readfirstlane(lv) != 0u)
+                return;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        __asm__ volatile("" ::: "memory");
+        const u32 *slot = W.ring + si * G::SLOT;
+        // everything the batch may need in one go: most of its time is LDS latency
+        u32 tw[B * NA], sw[G::STATES ? N : 1][B], x0[N], muw[G::MUW];
+        get_words<B * NA>(slot + G::O_L, lane, tw);
+        const v4u on = *(const v4u *)(ctl->lanes + 4 * si);
+        if constexpr (G::STATES) {
+#pragma unroll
+            for (int s = 0; s < N; ++s)
+                get_words<B>(slot + G::O_X + G::XS * s, lane, sw[s]);
+        } else {
+#pragma unroll
+            for (int s = 0; s < N; ++s)
+                x0[s] = slot[G::O_X + 64 * s + lane];
+#pragma unroll
+            for (int q = 0; q < G::MUW; ++q)
+                muw[q] = slot[G::O_MU + 64 * q + lane];
+        }
+        const u64 act = ((u64)(u32)__builtin_amdgcn_readfirstlane(on.y) << 32) |
+                        (u64)(u32)__builtin_amdgcn_readfirstlane(on.x);
+        if (__builtin_expect(__builtin_amdgcn_readfirstlane(on.z) != 0, 0)) {
+            const u64 rm = ((u64)ctl_ld(&ctl->rmask[1]) << 32) | ctl_ld(&ctl->rmask[0]);
+            if (in_mask(rm)) {
+                k = (i32)W.tab[G::T_K + lane];
+                row = I.snap + (u64)(k - L.k_lo) * N * I.E + W.tab[G::T_IDX + lane];
+                t_next = k < L.k_hi ? row_time(k) : (Tm)SSA_INF_F;
+                t_after = k + 1 < L.k_hi ? row_time(k + 1) : (Tm)SSA_INF_F;
+            }
+            lds_fence();
+        }
+        Tm tn[B], t_max = (Tm)(-SSA_INF_F);
+#pragma unroll
+        for (int e = 0; e < B; ++e) {
+            tn[e] = (Tm)value_at<A>(tw, e);
+            t_max = tn[e] > t_max ? tn[e] : t_max;
+        }
+        if ((act & lanes(t_next < t_max)) != 0) {
+            u32 xw[N][B];   // states before each event
+            if constexpr (G::STATES) {
+#pragma unroll
+                for (int s = 0; s < N; ++s)
+#pragma unroll
+                    for (int e = 0; e < B; ++e)
+                        xw[s][e] = sw[s][e];
+            } else {
+                i32 x[N];
+#pragma unroll
+                for (int s = 0; s < N; ++s)
+                    x[s] = (i32)x0[s];
+#pragma unroll
+                for (int e = 0; e < B; ++e) {
+#pragma unroll
+                    for (int s = 0; s < N; ++s)
+                        xw[s][e] = (u32)x[s];
+                    if (e + 1 < B)
+                        Md::update(x, (int)((muw[e / G::MUPER] >> (G::MUB * (e % G::MUPER))) & ((1u << G::MUB) - 1u)));
+                }
+            }
+            // One row a lane and turn, every lane at its own event. Where only a lane or
+            // two are left, each with a wait that spans many rows (a promoter that is off
+            // for twenty of them), the whole wave writes that lane's rows, one a lane.
+            for (;;) {
+                const u64 cross = act & lanes(t_next < t_max);
+                if (cross == 0)
+                    break;
+                i32 xs[N];   // the state before the first event after t_next, and its time
+                Tm at = tn[B - 1];
+#pragma unroll
+                for (int s = 0; s < N; ++s)
+                    xs[s] = (i32)xw[s][B - 1];
+#pragma unroll
+                for (int e = B - 2; e >= 0; --e) {
+                    const bool here = t_next < tn[e];
+                    at = here ? tn[e] : at;
+#pragma unroll
+                    for (int s = 0; s < N; ++s)
+                        xs[s] = here ? (i32)xw[s][e] : xs[s];
+                }
+                const u64 more = cross & lanes(t_after < at);   // a second row at the same event
+                if (more != 0 && __popcll(cross) <= 2) {
+                    const u32 j = (u32)__ffsll((long long)cross) - 1u;
+                    const i32 kj = __builtin_amdgcn_readlane(k, j);
+                    const u64 rj = ((u64)(u32)__builtin_amdgcn_readlane((u32)((u64)row >> 32), j) << 32) |
+                                   (u64)(u32)__builtin_amdgcn_readlane((u32)(u64)row, j);
+                    Tm aj;
+                    if constexpr (sizeof(Tm) == 8) {
+                        const u64 ab = __builtin_bit_cast(u64, at);
+                        aj = __builtin_bit_cast(Tm, ((u64)(u32)__builtin_amdgcn_readlane((u32)(ab >> 32), j) << 32) |
+                                                        (u64)(u32)__builtin_amdgcn_readlane((u32)ab, j));
+                    } else {
+                        aj = __builtin_bit_cast(Tm, __builtin_amdgcn_readlane(__builtin_bit_cast(u32, at), j));
+                    }
+                    const u64 stored = lanes(row_time(kj + (i32)lane) < aj);   // times ascend: its first lanes
+                    i32 *const to = (i32 *)rj + (u64)lane * ((u64)N * I.E);
+#pragma unroll
+                    for (int s = 0; s < N; ++s) {
+                        const i32 xj = __builtin_amdgcn_readlane(xs[s], j);
+                        if (in_mask(stored))
+                            to[(u64)s * I.E] = xj;
+                    }
+                    if (lane == j) {
+                        const u32 cnt = (u32)__popcll(stored);
+                        row += (u64)cnt * N * I.E;
+                        k += (i32)cnt;
+                        t_next = row_time(k);
+                        t_after = row_time(k + 1);
+                    }
+                } else if (in_mask(cross)) {
+#pragma unroll
+                    for (int s = 0; s < N; ++s)
+                        row[(u64)s * I.E] = xs[s];
+                    row += (u64)N * I.E;
+                    ++k;
+                    t_next = t_after;
+                    t_after = row_time(k + 1);
+                }
+            }
+        }
+        lds_fence();
+        lds_st(&ctl->done_s, b + 1u);
+        si_next = si + 1u == W.nb ? 0u : si + 1u;
+    }
+}
+
+template <class P, class Md, bool HALF, bool PER_LANE_RATES>
+__device__ __forceinline__ void pipe_item(const LaunchArgs &L, const ItemArgs &I, const PipeWg &W0, u32 words, u32 role)
+{
+    typedef PipeGeom<P, Md, HALF> G;
+    PipeWg W = W0;
+    W.nb = G::batches(words);
+    W.tab = W.ring + W.nb * (u32)G::SLOT;
+    if (role == 0u) {
+        __builtin_amdgcn_s_setprio(3);
+        pipe_events<P, Md, HALF, PER_LANE_RATES>(L, I, W);
+    } else if (role == 1u) {
+        __builtin_amdgcn_s_setprio(2);
+        pipe_clock<P, Md, HALF, PER_LANE_RATES>(L, I, W);
+    } else if (role == 3u) {
+        __builtin_amdgcn_s_setprio(2);
+        pipe_rows<P, Md, HALF>(L, I, W);
+    } else {
+        pipe_draw<P, Md, HALF>(L, W);
     }
 }
 
