@@ -1672,7 +1672,10 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
                 else
                     target = u2 * a0;
                 // past[j]: the reaction comes after j (partial sums never fall, so the
-                // first false one names it)
+                // first false one names it). A target rounded up to the total selects the
+                // last reaction that can fire: the last of all, where that one can (a
+                // 16-bit target is one in most bfloat16 batches and a fifth of the fp16
+                // ones of 64 lanes and 8 events); else the batch is computed again.
                 bool past[M];
 #pragma unroll
                 for (int j = 0; j < M; ++j)
@@ -1688,10 +1691,10 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
                     Md::update(x, mu);
                     muw[e / G::MUPER] |= (u32)mu << (G::MUB * (e % G::MUPER));
                 } else if constexpr (G::STATES) {
-                    again |= lanes(past[M - 1]);
+                    again |= lanes(past[M - 1]) & ~(P::UNI ? lanes(a[M - 1] > (T)0) : 0ull);
                     Md::advance(x, past);
                 } else {
-                    again |= lanes(past[M - 1]);
+                    again |= lanes(past[M - 1]) & ~(P::UNI ? lanes(a[M - 1] > (T)0) : 0ull);
                     const int mu = Md::reaction(past);
                     Md::update(x, mu);
                     muw[e / G::MUPER] |= (u32)mu << (G::MUB * (e % G::MUPER));

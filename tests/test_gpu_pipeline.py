@@ -103,3 +103,18 @@ def test_records_beside_refills(gpu, orc, mode):
     # a record of 5 entries overflows in some trajectories and stays empty in others
     run_records(gpu, orc, wl.telegraph(0.05, 0.05, 20.0, 1.0), np.array([1, 0, 0], np.int32), 700, 30.0,
                 [10.0, 30.0], mode, 0b11, 5, seed=3, block_size=512, grid_size=1)
+
+
+@pytest.mark.parametrize("mode", ["UNI_BF16_SR", "UNI_F16_SR", "UNI_BF16_SR_NORM", "UNI_BF16_RTN"])
+def test_targets_rounded_up_to_the_total(gpu, orc, mode):
+    # such a target selects the last reaction that can fire: here the last of all can in
+    # some events only (Y is mostly zero), and X is always the last but one
+    m = wl._build("tail", ["X", "Y"], [
+        {"change": {"X": +1}, "k": 20.0},
+        {"reactants": {"X": 1}, "change": {"Y": +1}, "k": 0.02},
+        {"reactants": {"X": 1}, "change": {"X": -1}, "k": 1.0},
+        {"reactants": {"Y": 1}, "change": {"Y": -1}, "k": 2.0},
+    ])
+    run, _, _ = run_both(gpu, orc, m, np.array([20, 0], np.int32), 640, 20.0, [10.0, 20.0], mode, seed=7,
+                         max_events=5000)
+    pipelined(run)
