@@ -723,9 +723,13 @@ struct SourceId {
     size_t size = 0;
 };
 
-// dynamic LDS of a pipelined workgroup with a CU to itself, and with half of one
-// (kPipeLds, kPipeLdsHalf in ssa_device.hip)
-constexpr unsigned kPipeLds = 150 * 1024, kPipeLdsHalf = 75 * 1024;
+// dynamic LDS of a workgroup of the pipelined kernels, two to a CU and one
+// (pipe_lds in ssa_device.hip)
+unsigned pipe_lds(int format, bool half)
+{
+    const bool wide = format == SSA_FMT_FP64;
+    return half ? (wide ? 75 * 1024 : 77 * 1024 + 512) : (wide ? 155 * 1024 : 157 * 1024);
+}
 
 struct Loaded {
     hipModule_t mod = nullptr;
@@ -823,8 +827,8 @@ int get_kernel(const ssa_run_desc *d, const SourceId &id, Loaded &out, bool load
                lds_static > 0 &&
                hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 512, lds) == hipSuccess && n >= want;
     };
-    ld.pl_ok = fits(ld.kernel_pl, kPipeLds, 1);
-    ld.ph_ok = fits(ld.kernel_ph, kPipeLdsHalf, 2);
+    ld.pl_ok = fits(ld.kernel_pl, pipe_lds(d->format, false), 1);
+    ld.ph_ok = fits(ld.kernel_ph, pipe_lds(d->format, true), 2);
     g_loaded[key] = ld;
     out = ld;
     return SSA_OK;
@@ -1314,7 +1318,7 @@ int launch_all(ssa_run *r, const ssa_run_desc *d, const Loaded &ld, int n_chunks
     A.h.max_events = d->max_events;
     A.h.place = r->place & SSA_PLACE_WAVE_MAJOR ? 2 : 0;   // PLACE_WAVE_MAJOR
     A.h.guard = r->guard ? 1u : 0u;
-    A.h.pipe_words = (r->pipe_two ? kPipeLdsHalf : kPipeLds) / 4;
+    A.h.pipe_words = pipe_lds(d->format, r->pipe_two) / 4;
     A.h.pipe_half = (uint32_t)ld.cus;
     const int nI = d->n_items;
     hipStream_t s = r->graph ? r->cap : r->stream;
@@ -1363,7 +1367,7 @@ int launch_all(ssa_run *r, const ssa_run_desc *d, const Loaded &ld, int n_chunks
             HIP_TRY(hipEventRecord(r->kev[2 * c], s));
         if (r->pipe)
             HIP_TRY(hipModuleLaunchKernel(r->pipe_two ? ld.kernel_ph : ld.kernel_pl, r->grid, 1, 1, 512, 1, 1,
-                                          r->pipe_two ? kPipeLdsHalf : kPipeLds, s, args, nullptr));
+                                          pipe_lds(d->format, r->pipe_two), s, args, nullptr));
         else
             HIP_TRY(hipModuleLaunchKernel(ld.kernel, r->grid, 1, 1, r->block, 1, 1, 0, s, args, nullptr));
         if (!r->kev.empty())

@@ -1137,8 +1137,13 @@ typedef u32 v2u __attribute__((ext_vector_type(2)));
 
 constexpr int kPipeBatches = 16;   // most batches of a ring
 constexpr int kSnapTable = 512;    // snapshot times kept in LDS
-constexpr int kPipeLds = 150 * 1024;       // ring and tables with a CU to one workgroup
-constexpr int kPipeLdsHalf = 75 * 1024;    // with two workgroups to a CU
+// bytes of ring and tables, with two workgroups to a CU and with one: a CU's 160 KB
+// without PipeCtl and the snapshot times (4.4 KB in binary64, 2.4 KB else)
+template <class P>
+constexpr int pipe_lds(bool half)
+{
+    return half ? (P::WIDE ? 75 * 1024 : 77 * 1024 + 512) : (P::WIDE ? 155 * 1024 : 157 * 1024);
+}
 
 struct __attribute__((aligned(16))) PipeCtl {
     u32 ready[kPipeBatches];
@@ -1216,14 +1221,16 @@ struct PipeGeom {
     static constexpr bool fits(int b, int n, int bytes) { return 4 * (n * slot_words(b) + TABLE) <= bytes; }
     // Batch length B: what a wave does once a batch is shared by B events, and the
     // event wave's straight-line code is that long. One workgroup to a CU (!HALF): the
-    // longest that leaves a ring of five batches. Two to a CU (HALF): four at most,
-    // so that eight fit and the draw waves keep several in hand.
+    // longest that leaves a ring of five batches. Two to a CU (HALF): four at most, with
+    // six, so that the draw waves keep several in hand (telegraph, 262k trajectories,
+    // 101 rows: UNI_BF16_SR 3.5 ms with six of four and 3.9 with eleven of two,
+    // UNI_F16_SR_NORM 4.8 with five of four and 4.5 with eleven of two).
     static constexpr int pick()
     {
         for (int b = HALF ? 4 : Md::M <= 12 ? 8 : Md::M <= 32 ? 4 : 2; b >= 2; b /= 2)
-            if (fits(b, HALF ? 6 : 5, HALF ? kPipeLdsHalf : kPipeLds))
+            if (fits(b, HALF ? 6 : 5, pipe_lds<P>(HALF)))
                 return b;
-        return fits(2, 4, HALF ? kPipeLdsHalf : kPipeLds) ? 2 : 0;
+        return fits(2, 4, pipe_lds<P>(HALF)) ? 2 : 0;
     }
     static constexpr bool OK = pick() != 0;
     static constexpr int B = OK ? pick() : 2;
