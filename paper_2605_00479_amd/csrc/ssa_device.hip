@@ -50,38 +50,81 @@ __device__ __forceinline__ u32 xor3(u32 a, u32 b, u32 c)
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);   // a ^ b ^ c in one VALU op
 }
 
-__device__ __forceinline__ W4 philox10(u32 c0, u32 c1, u32 c2, u32 c3, u32 k0, u32 k1)
+// Rounds FROM .. 9 on the counter c.
+template <int FROM>
+__device__ __forceinline__ W4 philox_rounds(W4 c, u32 k0, u32 k1)
 {
+    k0 += FROM * 0x9E3779B9u;
+    k1 += FROM * 0xBB67AE85u;
 #pragma unroll
-    for (int r = 0; r < 10; ++r) {
-        u64 p0 = (u64)0xD2511F53u * (u64)c0;
-        u64 p1 = (u64)0xCD9E8D57u * (u64)c2;
-        u32 n0 = xor3((u32)(p1 >> 32), c1, k0);
-        u32 n2 = xor3((u32)(p0 >> 32), c3, k1);
-        c1 = (u32)p1;
-        c3 = (u32)p0;
-        c0 = n0;
-        c2 = n2;
+    for (int r = FROM; r < 10; ++r) {
+        const u64 p0 = (u64)0xD2511F53u * (u64)c.w0;
+        const u64 p1 = (u64)0xCD9E8D57u * (u64)c.w2;
+        c = {xor3((u32)(p1 >> 32), c.w1, k0), (u32)p1, xor3((u32)(p0 >> 32), c.w3, k1), (u32)p0};
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
     }
-    W4 o = {c0, c1, c2, c3};
-    return o;
+    return c;
 }
+
+// The generator of one trajectory: counter (n, id, stream), key (k0, k1).
+struct Philox {
+    u32 id, k0, k1;
+    __device__ __forceinline__ W4 operator()(u64 n, u32 stream) const
+    {
+        return philox_rounds<0>({(u32)n, (u32)(n >> 32), id, stream}, k0, k1);
+    }
+};
+
+// The same for event indices that share their upper word: half of the first round's
+// products and half of the second's depend on the trajectory and that word alone.
+struct PhiloxNear {
+    u32 k0, k1, lo1, hi2, lo2;
+    __device__ __forceinline__ PhiloxNear(const Philox &g, u32 n_hi)
+    {
+        const u64 p1 = (u64)0xCD9E8D57u * (u64)g.id;
+        const u64 p0 = (u64)0xD2511F53u * (u64)xor3((u32)(p1 >> 32), n_hi, g.k0);
+        k0 = g.k0;
+        k1 = g.k1;
+        lo1 = (u32)p1;
+        hi2 = (u32)(p0 >> 32) ^ (g.k1 + 0xBB67AE85u);
+        lo2 = (u32)p0;
+    }
+    __device__ __forceinline__ W4 operator()(u64 n, u32 stream) const
+    {
+        const u64 p0 = (u64)0xD2511F53u * (u64)(u32)n;
+        const u64 p1 = (u64)0xCD9E8D57u * (u64)((u32)(p0 >> 32) ^ (stream ^ k1));
+        return philox_rounds<2>({xor3((u32)(p1 >> 32), lo1, k0 + 0x9E3779B9u), (u32)p1, hi2 ^ (u32)p0, lo2}, k0, k1);
+    }
+};
+
+// Constants of the draws that are no inline operands. A kernel that keeps them in
+// registers (pin) spares the copies that the two-operand multiply-add and the
+// one-scalar limit of an instruction ask for.
+struct DrawConst {
+    double ulp53 = 0x1p-53, c19 = 0x1.af286bca1af28p-5;
+    float ulp24 = 0x1p-24f;
+    u32 mant64 = 0xFFFFFu, one64 = 0x3FF00000u, mant32 = 0x7FFFFFu, one32 = 0x3F800000u;
+    __device__ __forceinline__ void pin()
+    {
+        __asm__ volatile("" : "+v"(ulp53), "+v"(c19), "+v"(ulp24), "+v"(one64), "+v"(one32));
+        __asm__ volatile("" : "+s"(mant64), "+s"(mant32));
+    }
+};
 
 // --------------------------------------------------------------------------
 // Uniforms on (0, 1]: (m + 1) 2^-53 from 53 bits, (m + 1) 2^-24 from 24 bits.
 // --------------------------------------------------------------------------
-__device__ __forceinline__ double unif53(u32 a, u32 b)
+__device__ __forceinline__ double unif53(u32 a, u32 b, const DrawConst &k = DrawConst())
 {
-    u64 m = ((u64)a << 21) | (u64)(b >> 11);
-    return (double)(m + 1ull) * 0x1p-53;
+    // m = a 2^21 + (b >> 11): every product and sum below is exact (m + 1 <= 2^53)
+    return __builtin_fma((double)a, 0x1p-32, __builtin_fma((double)(b >> 11), k.ulp53, k.ulp53));
 }
 
-__device__ __forceinline__ float unif24(u32 w)
+__device__ __forceinline__ float unif24(u32 w, const DrawConst &k = DrawConst())
 {
     // (m + 1) 2^-24 = m 2^-24 + 2^-24, exact in binary32 for m < 2^24
-    return __builtin_fmaf((float)(w >> 8), 0x1p-24f, 0x1p-24f);
+    return __builtin_fmaf((float)(w >> 8), k.ulp24, k.ulp24);
 }
 
 // --------------------------------------------------------------------------
@@ -141,19 +184,18 @@ __device__ __forceinline__ float div_rn_inrange(float a, float b)
 // fixed order: the quotient s, the series by Horner's rule in fmas, ln f =
 // fma(2s, p z, 2s), and fma(e, ln2_hi, fma(e, ln2_lo, ln f)).
 // --------------------------------------------------------------------------
-__device__ __forceinline__ double neg_log64(double u)
+__device__ __forceinline__ double neg_log64(double u, const DrawConst &k = DrawConst())
 {
-    u64 bits = (u64)__double_as_longlong(u);
-    int e = (int)((bits >> 52) & 0x7FFull) - 1023;
-    double f = __longlong_as_double((i64)((bits & 0x000FFFFFFFFFFFFFull) | 0x3FF0000000000000ull));
-    if (f > 0x1.6a09e667f3bcdp+0) {
-        f = f * 0.5;
-        e = e + 1;
-    }
-    double s = div_rn_log64(f - 1.0, f + 1.0);
+    const u64 bits = (u64)__double_as_longlong(u);
+    const u32 hi = (u32)(bits >> 32);
+    const double g = __longlong_as_double((i64)(((u64)((hi & k.mant64) | k.one64) << 32) | (bits & 0xFFFFFFFFull)));
+    const bool big = g > 0x1.6a09e667f3bcdp+0;
+    const int e = (int)(hi >> 20) + (big ? -1022 : -1023);
+    const double h = __longlong_as_double((i64)(big ? 0x3FE0000000000000ull : 0x3FF0000000000000ull));
+    double s = div_rn_log64(__builtin_fma(g, h, -1.0), __builtin_fma(g, h, 1.0));   // f = g h, exact
     double z = s * s;
     double p = 0x1.8618618618618p-5;         // 1/21
-    p = __builtin_fma(p, z, 0x1.af286bca1af28p-5); // 1/19
+    p = __builtin_fma(p, z, k.c19);          // 1/19
     p = __builtin_fma(p, z, 0x1.e1e1e1e1e1e1ep-5); // 1/17
     p = __builtin_fma(p, z, 0x1.1111111111111p-4); // 1/15
     p = __builtin_fma(p, z, 0x1.3b13b13b13b14p-4); // 1/13
@@ -166,20 +208,17 @@ __device__ __forceinline__ double neg_log64(double u)
     double s2 = s + s;
     double lnf = __builtin_fma(s2, p, s2);
     double ed = (double)e;
-    double r = __builtin_fma(ed, 0x1.62e42fep-1, __builtin_fma(ed, 0x1.f473de6af278fp-30, lnf));
-    return 0.0 - r;
+    return __builtin_fma(-ed, 0x1.62e42fep-1, -__builtin_fma(ed, 0x1.f473de6af278fp-30, lnf));
 }
 
-__device__ __forceinline__ float neg_log32(float u)
+__device__ __forceinline__ float neg_log32(float u, const DrawConst &k = DrawConst())
 {
-    u32 bits = __float_as_uint(u);
-    int e = (int)((bits >> 23) & 0xFFu) - 127;
-    float f = __uint_as_float((bits & 0x7FFFFFu) | 0x3F800000u);
-    if (f > 0x1.6a09e6p+0f) {
-        f = f * 0.5f;
-        e = e + 1;
-    }
-    float s = div_rn_log(f - 1.0f, f + 1.0f);   // f in [1/sqrt2, sqrt2]
+    const u32 bits = __float_as_uint(u);
+    const float g = __uint_as_float((bits & k.mant32) | k.one32);
+    const bool big = g > 0x1.6a09e6p+0f;
+    const int e = (int)(bits >> 23) + (big ? -126 : -127);
+    const float h = big ? 0.5f : 1.0f;
+    float s = div_rn_log(__builtin_fmaf(g, h, -1.0f), __builtin_fmaf(g, h, 1.0f));   // f = g h, exact
     float z = s * s;
     float p = 0x1.c71c72p-4f;                 // 1/9
     p = __builtin_fmaf(p, z, 0x1.24924ap-3f); // 1/7
@@ -189,8 +228,7 @@ __device__ __forceinline__ float neg_log32(float u)
     float s2 = s + s;
     float lnf = __builtin_fmaf(s2, p, s2);
     float ed = (float)e;
-    float r = __builtin_fmaf(ed, 0x1.62e4p-1f, __builtin_fmaf(ed, 0x1.7f7d1cp-20f, lnf));
-    return 0.0f - r;
+    return __builtin_fmaf(-ed, 0x1.62e4p-1f, -__builtin_fmaf(ed, 0x1.7f7d1cp-20f, lnf));
 }
 
 // --------------------------------------------------------------------------
@@ -468,13 +506,13 @@ struct ConvPool {
 };
 
 // Conversion fields of event n (drawn only when a count is not exactly representable).
-template <int NCONV, int B>
-__device__ __forceinline__ ConvPool<NCONV, B> make_conv(u64 n, u32 id, u32 k0, u32 k1)
+template <int NCONV, int B, class Gen>
+__device__ __forceinline__ ConvPool<NCONV, B> make_conv(const Gen &gen, u64 n)
 {
     ConvPool<NCONV, B> cp;
 #pragma unroll
     for (int q = 0; q < ConvPool<NCONV, B>::NSTREAM; ++q) {
-        W4 r = philox10((u32)n, (u32)(n >> 32), id, SSA_CONV_STREAM + (u32)q, k0, k1);
+        W4 r = gen(n, SSA_CONV_STREAM + (u32)q);
         cp.w[4 * q + 0] = r.w0;
         cp.w[4 * q + 1] = r.w1;
         cp.w[4 * q + 2] = r.w2;
@@ -501,18 +539,18 @@ struct Draw {
     typename P::A u2;
 };
 
-template <class P, int NSLOT, int SLOT_LOG>
-__device__ __forceinline__ Draw<P, NSLOT> make_draw(u64 n, u32 id, u32 k0, u32 k1)
+template <class P, int NSLOT, int SLOT_LOG, class Gen>
+__device__ __forceinline__ Draw<P, NSLOT> make_draw(const Gen &gen, u64 n, const DrawConst &k = DrawConst())
 {
     Draw<P, NSLOT> d;
-    W4 r0 = philox10((u32)n, (u32)(n >> 32), id, 0u, k0, k1);
+    W4 r0 = gen(n, 0u);
     if constexpr (NSLOT > 0) {
         d.pool.w[0] = r0.w2;
         d.pool.w[1] = r0.w3;
         d.pool.w[2] = (r0.w0 & 0xFFu) | ((r0.w1 & 0xFFu) << 8);
 #pragma unroll
         for (int q = 1; q < Pool<NSLOT, P::SR_B>::NSTREAM; ++q) {
-            W4 rq = philox10((u32)n, (u32)(n >> 32), id, (u32)q, k0, k1);
+            W4 rq = gen(n, (u32)q);
             d.pool.w[3 + 4 * (q - 1) + 0] = rq.w0;
             d.pool.w[3 + 4 * (q - 1) + 1] = rq.w1;
             d.pool.w[3 + 4 * (q - 1) + 2] = rq.w2;
@@ -520,11 +558,11 @@ __device__ __forceinline__ Draw<P, NSLOT> make_draw(u64 n, u32 id, u32 k0, u32 k
         }
     }
     if constexpr (P::WIDE) {
-        d.L = neg_log64(unif53(r0.w0, r0.w1));
-        d.u2 = unif53(r0.w2, r0.w3);
+        d.L = neg_log64(unif53(r0.w0, r0.w1, k), k);
+        d.u2 = unif53(r0.w2, r0.w3, k);
     } else {
-        d.L = P::arnd(neg_log32(unif24(r0.w0)), d.pool.hw(SLOT_LOG));
-        d.u2 = unif24(r0.w1);
+        d.L = P::arnd(neg_log32(unif24(r0.w0, k), k), d.pool.hw(SLOT_LOG));
+        d.u2 = unif24(r0.w1, k);
     }
     return d;
 }
@@ -865,7 +903,7 @@ __device__ void run_item(const LaunchArgs &L, const ItemArgs &I, u32 slot_rank, 
                         t_next = k < L.k_hi ? snap_time<P>(L, k) : (Tm)SSA_INF_F;
                         t_stop = (!L.last && k >= L.k_hi) ? (Tm)(-SSA_INF_F) : t_end;
                         n_claim = n;
-                        cur = make_draw<P, NSLOT, SLOT_LOG>(n, I.id_base + id, L.seed_lo, L.seed_hi);
+                        cur = make_draw<P, NSLOT, SLOT_LOG>(Philox{I.id_base + id, L.seed_lo, L.seed_hi}, n);
                     }
                 }
                 if (base + cnt >= I.E)
@@ -894,7 +932,7 @@ __device__ void run_item(const LaunchArgs &L, const ItemArgs &I, u32 slot_rank, 
                 constexpr int V = decltype(vtag)::value;
                 // ---- draws: cur belongs to event n; event n+1's is formed alongside
                 const u32 id = I.id_base + idx;
-                const Draw<P, NSLOT> nxt = make_draw<P, NSLOT, SLOT_LOG>(n + 1, id, L.seed_lo, L.seed_hi);
+                const Draw<P, NSLOT> nxt = make_draw<P, NSLOT, SLOT_LOG>(Philox{id, L.seed_lo, L.seed_hi}, n + 1);
                 const Pool<NSLOT, P::SR_B> &pool = cur.pool;
                 // ---- propensities (generated op sequence) in version V.
                 // Conversions of counts draw random bits only when they round:
@@ -910,7 +948,7 @@ __device__ void run_item(const LaunchArgs &L, const ItemArgs &I, u32 slot_rank, 
                     Md::template propensities<P, VS::CONV, true>(x, c, hill, a, pool, NoConv());
                 } else {
                     const ConvPool<Md::NCONV, P::SR_B> cpool =
-                        make_conv<Md::NCONV, P::SR_B>(n, id, L.seed_lo, L.seed_hi);
+                        make_conv<Md::NCONV, P::SR_B>(Philox{id, L.seed_lo, L.seed_hi}, n);
                     Md::template propensities<P, false, V == VER_CONV>(x, c, hill, a, pool, cpool);
                 }
                 // ---- optional running-max normalisation (uniform 16-bit)
@@ -1398,6 +1436,8 @@ __device__ void pipe_draw(const LaunchArgs &L, const PipeWg &W)
     PipeCtl *ctl = W.ctl;
     u32 gen = 0, id = 0, si = 0, sw = 0;
     u64 off = 0, b64 = 0;
+    DrawConst con;
+    con.pin();
     for (;;) {
         u32 nb = 0;
         if (lane == 0)
@@ -1428,58 +1468,65 @@ __device__ void pipe_draw(const LaunchArgs &L, const PipeWg &W)
         }
         u32 *slot = W.ring + si * G::SLOT;
         const u64 n0 = off + b64 * B;
+        const Philox any{id, L.seed_lo, L.seed_hi};
+        auto draws = [&](const auto &rng) __attribute__((always_inline)) {
 #pragma unroll
-        for (int e0 = 0; e0 < B; e0 += GR) {
-            Draw<P, S::NSLOT> d[GR];
+            for (int e0 = 0; e0 < B; e0 += GR) {
+                Draw<P, S::NSLOT> d[GR];
 #pragma unroll
-            for (int e = 0; e < GR; ++e)
-                d[e] = make_draw<P, S::NSLOT, S::LOG>(n0 + (u64)(e0 + e), id, L.seed_lo, L.seed_hi);
-            u32 lw[GR * NA], uw[GR * NA];
-#pragma unroll
-            for (int e = 0; e < GR; ++e) {
-                value_to<A>(lw, e, d[e].L);
-                value_to<A>(uw, e, d[e].u2);
-            }
-            put_words<GR * NA>(slot + G::O_L + 64 * e0 * NA, lane, lw);
-            if constexpr (G::POOL) {
+                for (int e = 0; e < GR; ++e)
+                    d[e] = make_draw<P, S::NSLOT, S::LOG>(rng, n0 + (u64)(e0 + e), con);
+                u32 lw[GR * NA], uw[GR * NA];
 #pragma unroll
                 for (int e = 0; e < GR; ++e) {
-                    u32 w[G::EW];
-#pragma unroll
-                    for (int k = 0; k < G::NPW; ++k)
-                        w[k] = d[e].pool.w[k];
-                    w[G::NPW] = uw[e];
-                    put_words<G::EW>(slot + G::O_EV + G::EVS * (e0 + e), lane, w);
+                    value_to<A>(lw, e, d[e].L);
+                    value_to<A>(uw, e, d[e].u2);
                 }
-                if constexpr (G::NF > 0) {
-                    u32 fw[GR * G::FW];
+                put_words<GR * NA>(slot + G::O_L + 64 * e0 * NA, lane, lw);
+                if constexpr (G::POOL) {
 #pragma unroll
                     for (int e = 0; e < GR; ++e) {
-                        const u32 time = d[e].pool.hw(S::TIME);
-                        if constexpr (G::NF == 1) {
-                            fw[e] = time;
-                        } else {
-                            fw[e * G::FW] = (time & 0xFFFF0000u) | (d[e].pool.hw(S::TAU) >> 16);
-                            if constexpr (G::NF == 3)
-                                fw[e * G::FW + 1] = d[e].pool.hw(S::TAUM);
-                        }
-                    }
-                    put_words<GR * G::FW>(slot + G::O_F + 64 * e0 * G::FW, lane, fw);
-                }
-            } else {
-                put_words<GR * NA>(slot + G::O_EV + 64 * e0 * NA, lane, uw);
-            }
-        }
-        if constexpr (G::CONV) {
-            if (conv) {
+                        u32 w[G::EW];
 #pragma unroll
-                for (int e = 0; e < B; ++e) {
-                    const ConvPool<Md::NCONV, P::SR_B> cv =
-                        make_conv<Md::NCONV, P::SR_B>(n0 + (u64)e, id, L.seed_lo, L.seed_hi);
-                    put_words<G::CW>(slot + G::O_CV + G::CVS * e, lane, cv.w);
+                        for (int k = 0; k < G::NPW; ++k)
+                            w[k] = d[e].pool.w[k];
+                        w[G::NPW] = uw[e];
+                        put_words<G::EW>(slot + G::O_EV + G::EVS * (e0 + e), lane, w);
+                    }
+                    if constexpr (G::NF > 0) {
+                        u32 fw[GR * G::FW];
+#pragma unroll
+                        for (int e = 0; e < GR; ++e) {
+                            const u32 time = d[e].pool.hw(S::TIME);
+                            if constexpr (G::NF == 1) {
+                                fw[e] = time;
+                            } else {
+                                fw[e * G::FW] = (time & 0xFFFF0000u) | (d[e].pool.hw(S::TAU) >> 16);
+                                if constexpr (G::NF == 3)
+                                    fw[e * G::FW + 1] = d[e].pool.hw(S::TAUM);
+                            }
+                        }
+                        put_words<GR * G::FW>(slot + G::O_F + 64 * e0 * G::FW, lane, fw);
+                    }
+                } else {
+                    put_words<GR * NA>(slot + G::O_EV + 64 * e0 * NA, lane, uw);
                 }
             }
-        }
+            if constexpr (G::CONV) {
+                if (conv) {
+#pragma unroll
+                    for (int e = 0; e < B; ++e) {
+                        const ConvPool<Md::NCONV, P::SR_B> cv = make_conv<Md::NCONV, P::SR_B>(rng, n0 + (u64)e);
+                        put_words<G::CW>(slot + G::O_CV + G::CVS * e, lane, cv.w);
+                    }
+                }
+            }
+        };
+        // no lane's event index carries into its upper word within the batch
+        if (__builtin_expect(lanes((u32)n0 > 0u - (u32)B) == 0, 1))
+            draws(PhiloxNear(any, (u32)(n0 >> 32)));
+        else
+            draws(any);
         lds_fence();
         lds_st(ctl->ready + si, (b + 1u) << 2 | (b == sw ? 2u : 0u) | (conv ? 1u : 0u));
     }
@@ -1645,7 +1692,7 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
                 }
                 T a[M];
                 if constexpr (G::CONV && KIND == 2) {
-                    const CP cp = make_conv<Md::NCONV, P::SR_B>(n + (u64)e, id, L.seed_lo, L.seed_hi);
+                    const CP cp = make_conv<Md::NCONV, P::SR_B>(Philox{id, L.seed_lo, L.seed_hi}, n + (u64)e);
                     Md::template propensities<P, false, true>(x, c, hill, a, pool, cp);
                 } else if constexpr (KIND == 2) {
                     Md::template propensities<P, false, true>(x, c, hill, a, pool, NoConv());
