@@ -291,6 +291,7 @@ struct PrecF64 {
     __device__ static T div(T a, T b, u32) { return a / b; }
     __device__ static T add(T a, T b, u32) { return a + b; }
     __device__ static A acc(A s, T a, u32) { return s + (A)a; }
+    __device__ static A acc(A s, T a, u32 rb, float) { return acc(s, a, rb); }
     __device__ static A arnd(A v, u32) { return v; }
     __device__ static A tacc(A v, u32) { return v; }
     __device__ static A tau_div(A l, A a0) { return l / a0; }
@@ -311,6 +312,7 @@ struct PrecF32 {
     __device__ static T div(T a, T b, u32) { return a / b; }
     __device__ static T add(T a, T b, u32) { return a + b; }
     __device__ static A acc(A s, T a, u32) { return s + a; }
+    __device__ static A acc(A s, T a, u32 rb, float) { return acc(s, a, rb); }
     __device__ static A arnd(A v, u32) { return v; }
     __device__ static A tacc(A v, u32) { return v; }
     __device__ static A tau_div(A l, A a0) { return l / a0; }
@@ -436,6 +438,18 @@ struct Prec16 {
             return (float)((_Float16)s + (_Float16)a);
         else
             return UNIF ? rnd16<FMT, SR_ACC>(add32<FMT>(s, a), rb) : add32<FMT>(s, a);
+    }
+    // The same with a 1 that the compiler cannot see: s + 1 a in one rounding is the
+    // sum, and the mixed multiply-add takes fp16 operands without their conversion
+    // (which folds into a sum with a plain 1).
+    __device__ static A acc(A s, T a, u32 rb, float one)
+    {
+        if constexpr (FMT == FMT_FP16 && SR_ACC) {
+            const float v = __builtin_fmaf(a, one, s);
+            return UNIF ? rnd16<FMT, SR_ACC>(v, rb) : v;
+        } else {
+            return acc(s, a, rb);
+        }
     }
     __device__ static A arnd(A v, u32 rb) { return UNIF ? rnd16<FMT, SR_OPS>(v, rb) : v; }
     __device__ static A tacc(A v, u32 rb) { return UNIF ? rnd16<FMT, SR_ACC>(v, rb) : v; }
@@ -1558,7 +1572,8 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
         for (int j = 0; j < M; ++j)
             c[j] = uniform_value(rates[j]);
     }
-    float mrun = 0.0f;
+    float mrun = 0.0f, one = 1.0f;
+    __asm__ volatile("" : "+v"(one));
     u32 convw = 0, tag = 0;
     u64 live = 0;
     bool more = true;
@@ -1718,7 +1733,7 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
                 sum[0] = (A)a[0];
 #pragma unroll
                 for (int j = 1; j < M; ++j)
-                    sum[j] = P::acc(sum[j - 1], a[j], pool.hw(S::SUM + j - 1));
+                    sum[j] = P::acc(sum[j - 1], a[j], pool.hw(S::SUM + j - 1), one);
                 const A a0 = sum[M - 1];
                 A target;
                 if constexpr (P::UNI)
