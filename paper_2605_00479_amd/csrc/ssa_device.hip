@@ -256,11 +256,12 @@ __device__ __forceinline__ float rne_bf16(float v)
 
 // The conversions write one 16-bit half of a register and keep the other; the
 // random operand (used once, dead afterwards) serves as that other half, so no
-// register needs clearing or copying.
+// register needs clearing or copying. With the bfloat16 in the upper half and zeros
+// in the lower one the register holds the value in binary32.
 __device__ __forceinline__ float sr_bf16(float v, u32 r)
 {
-    ssa_v2bf16 o = __builtin_amdgcn_cvt_sr_bf16_f32(__builtin_bit_cast(ssa_v2bf16, r), v, r, false);
-    return (float)o[0];
+    const u32 h = r & 0xFFFF0000u;   // (no instruction where the field was shifted up)
+    return __builtin_bit_cast(float, __builtin_amdgcn_cvt_sr_bf16_f32(__builtin_bit_cast(ssa_v2bf16, h), v, h, true));
 }
 
 __device__ __forceinline__ float sr_f16(float v, u32 r)
