@@ -33,6 +33,7 @@
 #include <map>
 #include <memory>
 #include <mutex>
+#include <numeric>
 #include <sstream>
 #include <string>
 #include <unordered_map>
@@ -90,6 +91,21 @@ double primary_constant(const Model &md, int j, double k)
     for (int s = 0; s < md.N; ++s)
         d *= factorial(md.order[(size_t)j * md.N + s]);
     return k / (double)d;
+}
+
+// Propensity of reaction j with constant k at the counts x (an estimate in binary64).
+double propensity(const Model &md, int j, double k, const int32_t *x)
+{
+    const ssa_law &L = md.law[j];
+    if (L.kind != SSA_LAW_MASS_ACTION) {
+        const double qh = std::pow(x[L.regulator] / L.K, L.h);
+        return L.basal + (L.kind == SSA_LAW_HILL_REPRESS ? k : k * qh) / (1.0 + qh);
+    }
+    double a = primary_constant(md, j, k);
+    for (int s = 0; s < md.N; ++s)
+        for (int i = 0; i < md.order[(size_t)j * md.N + s]; ++i)
+            a *= std::max(0.0, (double)x[s] - i);
+    return a;
 }
 
 // Round-to-nearest-even of a binary64 value onto a floating grid with p
@@ -501,7 +517,9 @@ std::string gen_source(const std::vector<const Model *> &models, const ModeSpec 
           << "  for (i32 i = (i32)threadIdx.x; i < kSnapTable + 2; i += 512)\n"
           << "    snap_t[i] = L.k_lo + i < L.k_hi ? snap_time<PrecRun>(L, L.k_lo + i) : (PrecRun::Tm)SSA_INF_F;\n"
           << "  PipeWg W = {&ctl, lds, lds, 0u, (const u32 *)snap_t};\n"
-          << "  u32 it = blockIdx.x % SSA_N_ITEMS;\n"
+          << "  u32 turn = 0;\n"
+          << "  for (u32 i = 1; i < SSA_N_ITEMS; ++i)\n"
+          << "    turn = blockIdx.x >= L.item[i].first_wg ? i : turn;\n"
           << "  for (u32 i = 0; i < SSA_N_ITEMS; ++i) {\n"
           << "    if (w == 0u) {\n"
           << "      if (lane < (u32)kPipeBatches) ctl.ready[lane] = 0u;\n"
@@ -509,7 +527,7 @@ std::string gen_source(const std::vector<const Model *> &models, const ModeSpec 
           << "      ctl.gen = 0u; ctl.convw = 0u; ctl.sw = 0u;\n"
           << "    }\n"
           << "    __syncthreads();\n"
-          << "    switch (it) {\n";
+          << "    switch (L.item[turn].turn) {\n";
         for (size_t i = 0; i < models.size(); ++i)
             o << "    case " << i << ": pipe_item<PrecRun, Md" << i << ", " << h << ", "
               << (per_lane_rates[i] ? "true" : "false") << ">(L, L.item[" << i
@@ -517,7 +535,7 @@ std::string gen_source(const std::vector<const Model *> &models, const ModeSpec 
         o << "    default: break;\n"
           << "    }\n"
           << "    __syncthreads();\n"
-          << "    it = it + 1 == SSA_N_ITEMS ? 0 : it + 1;\n"
+          << "    turn = turn + 1 == SSA_N_ITEMS ? 0 : turn + 1;\n"
           << "  }\n"
           << "  }\n"
           << "}\n";
@@ -919,6 +937,8 @@ struct ItemArgsH {
     uint32_t traj_per_set;
     uint32_t id_base;
     uint32_t rec_cap;
+    uint32_t turn;
+    uint32_t first_wg;
 };
 
 constexpr int kMaxItems = 8;
@@ -1124,6 +1144,7 @@ struct ItemBuf {
     uint32_t rec_cap = 0;
     uint32_t traj_per_set = 0;
     uint32_t id_base = 0;
+    double pace = 0.0;           // event rate at the start times the work of an event
 };
 
 struct ssa_run {
@@ -1320,6 +1341,20 @@ int launch_all(ssa_run *r, const ssa_run_desc *d, const Loaded &ld, int n_chunks
     A.h.guard = r->guard ? 1u : 0u;
     A.h.pipe_words = pipe_lds(d->format, r->pipe_two) / 4;
     A.h.pipe_half = (uint32_t)ld.cus;
+    // The pipelined kernel takes the items by their pace, the longest chains first, and a
+    // workgroup starts at the first one that earlier workgroups do not fill: a long chain
+    // begun late ends the launch alone (five networks in MIX_BF16_SR, workgroups spread
+    // over the items and this: 20k trajectories each 111.0 and 106.7 ms, 13k each 10.1
+    // and 8.6 ms).
+    std::vector<uint32_t> turn(r->items.size()), first_wg(r->items.size());
+    std::iota(turn.begin(), turn.end(), 0u);
+    std::stable_sort(turn.begin(), turn.end(),
+                     [&](uint32_t p, uint32_t q) { return r->items[p].pace > r->items[q].pace; });
+    uint64_t wgs = 0;
+    for (size_t i = 0; i < turn.size(); ++i) {
+        first_wg[i] = (uint32_t)std::min<uint64_t>(wgs, UINT32_MAX);
+        wgs += ((uint64_t)r->items[turn[i]].E + 63) / 64;
+    }
     const int nI = d->n_items;
     hipStream_t s = r->graph ? r->cap : r->stream;
     // one zeroed counter per (chunk, item)
@@ -1361,6 +1396,8 @@ int launch_all(ssa_run *r, const ssa_run_desc *d, const Loaded &ld, int n_chunks
             ia.E = (uint32_t)b.E;
             ia.traj_per_set = b.traj_per_set;
             ia.id_base = b.id_base;
+            ia.turn = turn[i];
+            ia.first_wg = first_wg[i];
         }
         void *args[] = {&A};
         if (!r->kev.empty())
@@ -1495,6 +1532,10 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
                 else
                     ((float *)rt)[sidx * md.M + j] = (float)v;
             }
+        // an event's work grows with the reactions (binary64, cycles: birth-death 172,
+        // repressilator 752 at twelve)
+        for (int j = 0; j < md.M; ++j)
+            b.pace += propensity(md, j, it.set_rates ? it.set_rates[j] : md.law[j].k, it.x0) * (md.M + 1);
         std::vector<char> htab((size_t)2 * md.M * tsz);
         char *ht = htab.data();
         for (int j = 0; j < md.M; ++j) {

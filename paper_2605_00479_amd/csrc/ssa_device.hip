@@ -608,6 +608,9 @@ struct ItemArgs {
     u32 traj_per_set;        // trajectories per rate set (0: one set)
     u32 id_base;             // Philox trajectory id of trajectory 0
     u32 rec_cap;             // records kept per trajectory
+    // pipelined kernels: the i-th item's turn is the item that comes i-th, and its
+    // first_wg the first workgroup that starts there
+    u32 turn, first_wg;
 };
 
 struct LaunchArgs {
