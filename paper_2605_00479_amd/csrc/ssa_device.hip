@@ -255,8 +255,9 @@ __device__ __forceinline__ float rne_bf16(float v)
 }
 
 // The conversions write one 16-bit half of a register and keep the other; the
-// random operand (used once, dead afterwards) serves as that other half, so no
-// register needs clearing or copying. With the bfloat16 in the upper half and zeros
+// random operand serves as that other half, so no register needs clearing or copying
+// where it is dead afterwards; where it is half of a word that holds two (SHARED), the
+// converted value does. With the bfloat16 in the upper half and zeros
 // in the lower one the register holds the value in binary32.
 __device__ __forceinline__ float sr_bf16(float v, u32 r)
 {
@@ -264,9 +265,11 @@ __device__ __forceinline__ float sr_bf16(float v, u32 r)
     return __builtin_bit_cast(float, __builtin_amdgcn_cvt_sr_bf16_f32(__builtin_bit_cast(ssa_v2bf16, h), v, h, true));
 }
 
+template <bool SHARED = false>
 __device__ __forceinline__ float sr_f16(float v, u32 r)
 {
-    ssa_v2f16 o = __builtin_amdgcn_cvt_sr_f16_f32(__builtin_bit_cast(ssa_v2f16, r), v, r, false);
+    const ssa_v2f16 keep = SHARED ? __builtin_bit_cast(ssa_v2f16, v) : __builtin_bit_cast(ssa_v2f16, r);
+    const ssa_v2f16 o = __builtin_amdgcn_cvt_sr_f16_f32(keep, v, r, false);
     return (float)o[0];
 }
 
@@ -277,6 +280,7 @@ __device__ __forceinline__ float sr_f16(float v, u32 r)
 enum { FMT_FP64 = 0, FMT_FP32 = 1, FMT_FP16 = 2, FMT_BF16 = 3 };
 
 struct PrecF64 {
+    typedef PrecF64 Packed;
     typedef double T;
     typedef double A;
     typedef double Tm;
@@ -299,6 +303,7 @@ struct PrecF64 {
 };
 
 struct PrecF32 {
+    typedef PrecF32 Packed;
     typedef float T;
     typedef float A;
     typedef float Tm;
@@ -330,11 +335,11 @@ __device__ __forceinline__ float f32_kept(float v)
     return v;
 }
 
-template <int FMT, bool SRM>
+template <int FMT, bool SRM, bool SHARED = false>
 __device__ __forceinline__ float rnd16(float v, u32 rb)
 {
     if constexpr (FMT == FMT_FP16)
-        return SRM ? sr_f16(v, rb) : rne_f16(v);
+        return SRM ? sr_f16<SHARED>(v, rb) : rne_f16(v);
     else
         return SRM ? sr_bf16(v, rb) : rne_bf16(v);
 }
@@ -365,8 +370,10 @@ __device__ __forceinline__ float add32(float a, float b)
         return a + b;
 }
 
-template <int FMT, int RND, bool UNIF, bool NRM>
+// SHARED: the event wave's fields come two to a word.
+template <int FMT, int RND, bool UNIF, bool NRM, bool SHARED = false>
 struct Prec16 {
+    typedef Prec16<FMT, RND, UNIF, NRM, true> Packed;
     typedef float T;
     typedef float A;
     typedef float Tm;
@@ -382,7 +389,7 @@ struct Prec16 {
         if constexpr (EXACT)
             return (float)v;
         else
-            return rnd16<FMT, SR_OPS>((float)v, rb);
+            return rnd16<FMT, SR_OPS, SHARED>((float)v, rb);
     }
     // (x - i) converted. With |x| within the exact-integer limit the binary32
     // subtraction of the converted x is exact, and x is converted once.
@@ -392,7 +399,7 @@ struct Prec16 {
         if constexpr (EXACT)
             return (float)x - (float)i;
         else
-            return rnd16<FMT, SR_OPS>((float)(x - i), rb);
+            return rnd16<FMT, SR_OPS, SHARED>((float)(x - i), rb);
     }
     // Round to nearest in fp16: the hardware's fp16 product and sum
     // (v_mul_f16, v_add_f16) are the correctly rounded results, equal to the
@@ -407,7 +414,7 @@ struct Prec16 {
         if constexpr (NATIVE16)
             return (float)((_Float16)a * (_Float16)b);
         else
-            return rnd16<FMT, SR_OPS>(mul32<FMT>(a, b), rb);
+            return rnd16<FMT, SR_OPS, SHARED>(mul32<FMT>(a, b), rb);
     }
     // fp16: both operands have 11 significant bits and lie in [2^-24, 2^16), or are
     // special. One remainder correction of a times the hardware reciprocal (1 ulp) is
@@ -425,20 +432,20 @@ struct Prec16 {
             return a / b;
         }
     }
-    __device__ static T div(T a, T b, u32 rb) { return rnd16<FMT, SR_OPS>(quotient(a, b), rb); }
+    __device__ static T div(T a, T b, u32 rb) { return rnd16<FMT, SR_OPS, SHARED>(quotient(a, b), rb); }
     __device__ static T add(T a, T b, u32 rb)
     {
         if constexpr (NATIVE16)
             return (float)((_Float16)a + (_Float16)b);
         else
-            return rnd16<FMT, SR_OPS>(add32<FMT>(a, b), rb);
+            return rnd16<FMT, SR_OPS, SHARED>(add32<FMT>(a, b), rb);
     }
     __device__ static A acc(A s, T a, u32 rb)
     {
         if constexpr (UNIF && FMT == FMT_FP16 && !SR_ACC)
             return (float)((_Float16)s + (_Float16)a);
         else
-            return UNIF ? rnd16<FMT, SR_ACC>(add32<FMT>(s, a), rb) : add32<FMT>(s, a);
+            return UNIF ? rnd16<FMT, SR_ACC, SHARED>(add32<FMT>(s, a), rb) : add32<FMT>(s, a);
     }
     // The same with a 1 that the compiler cannot see: s + 1 a in one rounding is the
     // sum, and the mixed multiply-add takes fp16 operands without their conversion
@@ -447,13 +454,13 @@ struct Prec16 {
     {
         if constexpr (FMT == FMT_FP16 && SR_ACC) {
             const float v = __builtin_fmaf(a, one, s);
-            return UNIF ? rnd16<FMT, SR_ACC>(v, rb) : v;
+            return UNIF ? rnd16<FMT, SR_ACC, SHARED>(v, rb) : v;
         } else {
             return acc(s, a, rb);
         }
     }
-    __device__ static A arnd(A v, u32 rb) { return UNIF ? rnd16<FMT, SR_OPS>(v, rb) : v; }
-    __device__ static A tacc(A v, u32 rb) { return UNIF ? rnd16<FMT, SR_ACC>(v, rb) : v; }
+    __device__ static A arnd(A v, u32 rb) { return UNIF ? rnd16<FMT, SR_OPS, SHARED>(v, rb) : v; }
+    __device__ static A tacc(A v, u32 rb) { return UNIF ? rnd16<FMT, SR_ACC, SHARED>(v, rb) : v; }
     // -ln(u1) / a0. With fp16 propensities a0 lies in [2^-24, 2^22] whenever
     // the event can fire (any other value only sets a status), and
     // -ln(u1) in {0} or [2^-24, 16.7]: the short division applies.
@@ -1210,6 +1217,15 @@ struct __attribute__((aligned(16))) PipeCtl {
     u32 live[2];    // lanes that hold one from batch sw on
 };
 
+template <bool C, class X, class Y>
+struct Choose {
+    typedef X type;
+};
+template <class X, class Y>
+struct Choose<false, X, Y> {
+    typedef Y type;
+};
+
 // Words that NW words of a lane take in LDS: 16-byte units [unit][lane], then the
 // rest as 4- or 8-byte units (three words take a 16-byte unit).
 __host__ __device__ constexpr int lds_words(int nw)
@@ -1238,7 +1254,29 @@ struct PipeGeom {
     static constexpr bool CONV = P::SR && !P::SELECTIVE && Md::NCONV > 0;
     // pool words that hold fields (80 bits of stream 0, then whole streams)
     static constexpr int F0 = 80 / P::SR_B, F1 = 128 / P::SR_B;
-    static constexpr int NPW = !POOL ? 0 : 3 + field_words(NSLOT - F0, P::SR_B, F1);
+    // fp16 with a CU to one workgroup: the draw waves, which wait most of the time there,
+    // pack the event wave's fields two to a word, which leaves it one shift for two
+    static constexpr bool PACK = !HALF && POOL && P::SR_B == 13;
+    static constexpr int NEF = P::UNI ? S::LOG + 1 : NSLOT;   // its fields (the last: the target's)
+    static constexpr int NPW = !POOL ? 0 : PACK ? (NEF + 1) / 2 : 3 + field_words(NSLOT - F0, P::SR_B, F1);
+    // the slot of packed field f
+    static constexpr int field_slot(int f) { return P::UNI && f == S::LOG ? S::TARGET : f; }
+    struct EventPool {
+        u32 w[NPW > 0 ? NPW : 1];
+        __device__ __forceinline__ u32 hw(int s) const
+        {
+            if constexpr (PACK) {
+                const int f = P::UNI && s >= S::LOG ? S::LOG : s;
+                return f >= NEF ? 0u : f % 2 ? w[f / 2] << 16 : w[f / 2];
+            } else {
+                Pool<NSLOT, P::SR_B> p;
+#pragma unroll
+                for (int k = 0; k < NPW; ++k)
+                    p.w[k] = w[k];
+                return p.hw(s);
+            }
+        }
+    };
     static constexpr int EW = NPW + 1;                                                     // with u2 (POOL)
     static constexpr int CW = CONV ? field_words(Md::NCONV, P::SR_B, F1) : 0;
     // rounding fields of the clock: waiting time, its quotient by the maximum, the
@@ -1506,8 +1544,13 @@ __device__ void pipe_draw(const LaunchArgs &L, const PipeWg &W)
                     for (int e = 0; e < GR; ++e) {
                         u32 w[G::EW];
 #pragma unroll
-                        for (int k = 0; k < G::NPW; ++k)
-                            w[k] = d[e].pool.w[k];
+                        for (int k = 0; k < G::NPW; ++k) {
+                            if constexpr (G::PACK)
+                                w[k] = (d[e].pool.hw(G::field_slot(2 * k)) & 0xFFFF0000u) |
+                                       (2 * k + 1 < G::NEF ? d[e].pool.hw(G::field_slot(2 * k + 1)) >> 16 : 0u);
+                            else
+                                w[k] = d[e].pool.w[k];
+                        }
                         w[G::NPW] = uw[e];
                         put_words<G::EW>(slot + G::O_EV + G::EVS * (e0 + e), lane, w);
                     }
@@ -1558,6 +1601,7 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
     typedef typename P::A A;
     typedef Slots<P, Md> S;
     typedef PipeGeom<P, Md, HALF> G;
+    typedef typename Choose<G::PACK, typename P::Packed, P>::type PE;   // of the propensities and sums
     constexpr int N = Md::N, M = Md::M, B = G::B, NA = G::NA;
     constexpr int FW = G::POOL ? G::EW : B * NA;   // words loaded as a batch starts
     typedef ConvPool<Md::NCONV, P::SR_B> CP;
@@ -1680,7 +1724,7 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
             }
 #pragma unroll
             for (int e = 0; e < B; ++e) {
-                Pool<S::NSLOT, P::SR_B> pool;
+                typename G::EventPool pool;
                 A u2;
                 if constexpr (G::POOL) {
 #pragma unroll
@@ -1712,15 +1756,15 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
                 T a[M];
                 if constexpr (G::CONV && KIND == 2) {
                     const CP cp = make_conv<Md::NCONV, P::SR_B>(Philox{id, L.seed_lo, L.seed_hi}, n + (u64)e);
-                    Md::template propensities<P, false, true>(x, c, hill, a, pool, cp);
+                    Md::template propensities<PE, false, true>(x, c, hill, a, pool, cp);
                 } else if constexpr (KIND == 2) {
-                    Md::template propensities<P, false, true>(x, c, hill, a, pool, NoConv());
+                    Md::template propensities<PE, false, true>(x, c, hill, a, pool, NoConv());
                 } else if constexpr (KIND == 1) {
                     CP cp;
                     get_words<G::CW>(slot + G::O_CV + G::CVS * e, lane, cp.w);
-                    Md::template propensities<P, false, Md::template needs_guard<P>()>(x, c, hill, a, pool, cp);
+                    Md::template propensities<PE, false, Md::template needs_guard<PE>()>(x, c, hill, a, pool, cp);
                 } else {
-                    Md::template propensities<P, G::CONV, Md::template needs_guard<P>()>(x, c, hill, a, pool, NoConv());
+                    Md::template propensities<PE, G::CONV, Md::template needs_guard<PE>()>(x, c, hill, a, pool, NoConv());
                 }
                 if constexpr (P::NORM) {
                     float mx = 0.0f;
@@ -1731,17 +1775,17 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
                     mw[e] = __float_as_uint(mrun);
 #pragma unroll
                     for (int j = 0; j < M; ++j)
-                        a[j] = P::div(a[j], mrun, pool.hw(S::NORM + j));
+                        a[j] = PE::div(a[j], mrun, pool.hw(S::NORM + j));
                 }
                 A sum[M];
                 sum[0] = (A)a[0];
 #pragma unroll
                 for (int j = 1; j < M; ++j)
-                    sum[j] = P::acc(sum[j - 1], a[j], pool.hw(S::SUM + j - 1), one);
+                    sum[j] = PE::acc(sum[j - 1], a[j], pool.hw(S::SUM + j - 1), one);
                 const A a0 = sum[M - 1];
                 A target;
                 if constexpr (P::UNI)
-                    target = P::arnd(f32_kept(u2 * a0), pool.hw(S::TARGET));
+                    target = PE::arnd(f32_kept(u2 * a0), pool.hw(S::TARGET));
                 else
                     target = u2 * a0;
                 // past[j]: the reaction comes after j (partial sums never fall, so the
