@@ -228,7 +228,11 @@ __device__ __forceinline__ float neg_log32(float u, const DrawConst &k = DrawCon
     float s2 = s + s;
     float lnf = __builtin_fmaf(s2, p, s2);
     float ed = (float)e;
-    return __builtin_fmaf(-ed, 0x1.62e4p-1f, -__builtin_fmaf(ed, 0x1.7f7d1cp-20f, lnf));
+    float r = __builtin_fmaf(-ed, 0x1.62e4p-1f, -__builtin_fmaf(ed, 0x1.7f7d1cp-20f, lnf));
+    // rounded here: a conversion to fp16 that follows would be one instruction with the
+    // multiply-add, which rounds once
+    __asm__("" : "+v"(r));
+    return r;
 }
 
 // --------------------------------------------------------------------------
