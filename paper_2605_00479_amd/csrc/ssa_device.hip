@@ -1198,6 +1198,14 @@ __device__ void run_item(const LaunchArgs &L, const ItemArgs &I, u32 slot_rank, 
 // restart is posted once the row wave has finished batch sw.
 // Every wait is for a counter of a wave that does not wait for the waiting one;
 // `leave` ends all waits when the item has no trajectory left.
+//
+// With a CU to itself a workgroup is bound by the event wave's chain, whose length is
+// its instructions (one wave issues one in about 5 cycles): Schloegl, 64 trajectories,
+// cycles an event: 163 in FP64, 243 in MIX_F16_SR, 381 in MIX_BF16_SR, where one wave
+// for all of an event took 840 in FP64 and one with its draws made elsewhere 510.
+// With two workgroups to a CU the vector units are the bound: busy in 96% of the cycles
+// in FP64, 87-93% in MIX_F16_SR (262k trajectories; 200 cycles a step of 64 events and
+// CU on Schloegl, 161 and 180 on the dimer).
 // --------------------------------------------------------------------------
 typedef u32 v4u __attribute__((ext_vector_type(4)));
 typedef u32 v2u __attribute__((ext_vector_type(2)));
@@ -1484,6 +1492,10 @@ __device__ __forceinline__ u32 ctl_ld(const u32 *p)
 }
 
 // ------------------------------------------------------------ draw waves
+// Bound by vector instructions, 88 a draw in FP64 (100 before PhiloxNear, DrawConst and
+// the shorter uniform and logarithm: dimer, 262k trajectories, 3.47 and 3.15 ms) and 78
+// in MIX_F16_SR, of which the generator takes 37. Four draws are formed together, five
+// waves share the batches: a lone event wave needs four of them in FP64.
 template <class P, class Md, bool HALF>
 __device__ void pipe_draw(const LaunchArgs &L, const PipeWg &W)
 {
@@ -1598,6 +1610,8 @@ __device__ void pipe_draw(const LaunchArgs &L, const PipeWg &W)
 }
 
 // ------------------------------------------------------------ event wave
+// The chain: bound by its own instructions, 32 (MIX_F16_SR Schloegl, fields packed) to
+// 170 (UNI_F16_SR repressilator) an event, and about 200 cycles a batch.
 template <class P, class Md, bool HALF, bool PER_LANE_RATES>
 __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg &W)
 {
@@ -1875,6 +1889,8 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
 }
 
 // ------------------------------------------------------------ clock wave
+// Has slack: it waits for the event wave 10 to 60% of the time, least in FP64, where a
+// division takes 8 instructions. Its rare work (ends, claims) is behind one test a batch.
 template <class P, class Md, bool HALF, bool PER_LANE_RATES>
 __device__ void pipe_clock(const LaunchArgs &L, const ItemArgs &I, const PipeWg &W)
 {
@@ -2198,6 +2214,9 @@ __device__ void pipe_clock(const LaunchArgs &L, const ItemArgs &I, const PipeWg 
 }
 
 // ------------------------------------------------------------ row wave
+// Mostly LDS latency: everything a batch may need is read in one go, and a batch without a
+// row is one comparison. It holds the ring where rows are dense (telegraph in FP64, a row
+// per 13 events and trajectory: 262k trajectories 1.2 ms with rows, 0.85 without).
 template <class P, class Md, bool HALF>
 __device__ void pipe_rows(const LaunchArgs &L, const ItemArgs &I, const PipeWg &W)
 {
