@@ -1620,14 +1620,15 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
         // A workgroup runs 64 trajectories at a time; a grid size asked for counts 256.
         // Up to one workgroup per CU each has a CU to itself, where a chain of events is
         // fastest. Beyond that two share a CU if its SIMDs would idle otherwise: the
-        // event wave of a 16-bit mode is the slower part (dimer, many full waves: 346
-        // cycles per 64 events of a CU alone, 222 in two; 1M telegraph trajectories 52.6
-        // and 29.7 ms), in FP64 the draws are, which already keep the SIMDs busy (200
-        // alone, 203-224 in two). Alone is better where the ends are long and ragged, each
-        // lane then having half as many waves beside it: FP64 in the first two rounds
-        // (Schloegl, 33,000: 1.8 and 2.3 ms), and sweeps or several networks, whose
-        // chains differ most, in the first eight (64k-trajectory dimer sweep 27.7 and 49.4
-        // ms, five networks of 20k 117 and 125; at 12 rounds 2.32 and 2.30).
+        // event wave of a 16-bit mode is the slower part (dimer, many full waves: 293
+        // cycles per 64 events of a CU alone, 180 in two; 1M telegraph trajectories 44.1
+        // and 28.1 ms), in FP64 the draws are, which keep the SIMDs busier (198 alone, 161
+        // in two). Alone is better where the ends are long and ragged, each lane then
+        // having half as many waves beside it: FP64 in the first two rounds (Schloegl,
+        // 33,000: 1.8 and 2.2 ms), and sweeps or several networks, whose chains differ
+        // most, in the first eight (64k-trajectory dimer sweep 26.7 and 46.8 ms, five
+        // networks of 20k 107.6 and 111.2; dimer MIX_F16_SR at 12 rounds 2.13 and 2.21,
+        // telegraph sweep 0.33 and 0.26).
         int64_t wgs = std::max<int64_t>(1, (total + 63) / 64);
         if (asked)
             wgs = std::min<int64_t>(wgs, 4 * (int64_t)asked);
