@@ -1198,6 +1198,13 @@ __device__ void run_item(const LaunchArgs &L, const ItemArgs &I, u32 slot_rank, 
 // restart is posted once the row wave has finished batch sw.
 // Every wait is for a counter of a wave that does not wait for the waiting one;
 // `leave` ends all waits when the item has no trajectory left.
+// Batch numbers have 64 bits: a lane that runs one trajectory for 2^32 batches meets
+// the lower word of the last sw again. The counters carry lower words only, which is
+// enough to tell batches of one ring apart; a wave that needs the number counts on.
+// The tables of a lane are written while the other waves may read them (a draw wave
+// whose batch lies before sw, the event wave's careful path): such a lane holds no
+// trajectory in the batches that they work on, so nobody reads what they make of it,
+// and a draw wave takes the tables again once it sees the new gen.
 //
 // With a CU to itself a workgroup is bound by the event wave's chain, whose length is
 // its instructions (one wave issues one in about 5 cycles): Schloegl, 64 trajectories,
@@ -1224,7 +1231,7 @@ struct __attribute__((aligned(16))) PipeCtl {
     u32 ready[kPipeBatches];
     u32 lanes[4 * kPipeBatches];   // clock to row wave: {lanes, restart} of a batch
     u32 done_e, done_c, done_s, next;
-    u32 gen, convw, sw, leave;
+    u32 gen, convw, leave, sw[2];   // sw: lower and upper word
     u32 rmask[2];   // lanes that start a trajectory at batch sw
     u32 live[2];    // lanes that hold one from batch sw on
 };
@@ -1506,8 +1513,8 @@ __device__ void pipe_draw(const LaunchArgs &L, const PipeWg &W)
     constexpr int GR = B < 4 ? B : 4;   // draws formed together: their chains overlap
     const u32 lane = lane_id();
     PipeCtl *ctl = W.ctl;
-    u32 gen = 0, id = 0, si = 0, sw = 0;
-    u64 off = 0, b64 = 0;
+    u32 gen = 0, id = 0, si = 0;
+    u64 off = 0, b64 = 0, sw = 0;
     DrawConst con;
     con.pin();
     for (;;) {
@@ -1534,7 +1541,7 @@ __device__ void pipe_draw(const LaunchArgs &L, const PipeWg &W)
         lds_fence();
         if (g != gen) {
             gen = g;
-            sw = ctl_ld(&ctl->sw);
+            sw = ((u64)ctl_ld(&ctl->sw[1]) << 32) | ctl_ld(&ctl->sw[0]);
             id = W.tab[G::T_ID + lane];
             off = ((u64)W.tab[G::T_HI + lane] << 32) | W.tab[G::T_LO + lane];
         }
@@ -1605,7 +1612,7 @@ __device__ void pipe_draw(const LaunchArgs &L, const PipeWg &W)
         else
             draws(any);
         lds_fence();
-        lds_st(ctl->ready + si, (b + 1u) << 2 | (b == sw ? 2u : 0u) | (conv ? 1u : 0u));
+        lds_st(ctl->ready + si, (b + 1u) << 2 | (b64 == sw ? 2u : 0u) | (conv ? 1u : 0u));
     }
 }
 
@@ -1671,7 +1678,8 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
         return;
     u32 si_next = 0;
     __asm__ volatile(".p2align 6");
-    for (u32 b = 0;; ++b) {
+    for (u64 b64 = 0;; ++b64) {
+        const u32 b = (u32)b64;
         const u32 si = (u32)__builtin_amdgcn_readfirstlane(si_next);   // b mod nb
         u32 *slot = W.ring + si * G::SLOT;
         u32 first[FW];   // event 0's words, or every u2: in flight while the batch is looked over
@@ -1728,7 +1736,7 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
                     x[s] = x0[s];
                 mrun = m_start;
                 id = W.tab[G::T_ID + lane];
-                n = (((u64)W.tab[G::T_HI + lane] << 32) | W.tab[G::T_LO + lane]) + (u64)b * B;
+                n = (((u64)W.tab[G::T_HI + lane] << 32) | W.tab[G::T_LO + lane]) + b64 * B;
 #pragma unroll
                 for (int k = 0; k < G::MUW; ++k)
                     muw[k] = 0u;
@@ -1910,7 +1918,8 @@ __device__ void pipe_clock(const LaunchArgs &L, const ItemArgs &I, const PipeWg 
     u64 off = 0;           // event e of batch b is event off + b B + e
     u64 cap_b = 0;         // batches from here on hold the event cap
     u64 n_claim = 0;
-    u32 idx = 0, rec_cnt = 0, gen = 0, sw = 0;
+    u32 idx = 0, rec_cnt = 0, gen = 0;
+    u64 sw = 0;
     u64 act = 0, hold = 0;   // lanes in a trajectory, lanes waiting for batch sw
     bool open = true, pending = false, changed = false;
     // past the last row of this launch a trajectory is suspended (the last launch: ends)
@@ -1999,13 +2008,14 @@ __device__ void pipe_clock(const LaunchArgs &L, const ItemArgs &I, const PipeWg 
             if (base + cnt >= I.E)
                 open = false;
         }
-        sw = (u32)at_batch;
+        sw = at_batch;
         gen += 1u;
         lds_st(&ctl->rmask[0], (u32)fresh);
         lds_st(&ctl->rmask[1], (u32)(fresh >> 32));
         lds_st(&ctl->live[0], (u32)(act | hold));
         lds_st(&ctl->live[1], (u32)((act | hold) >> 32));
-        lds_st(&ctl->sw, sw);
+        lds_st(&ctl->sw[0], (u32)sw);
+        lds_st(&ctl->sw[1], (u32)(sw >> 32));
         lds_fence();
         lds_st(&ctl->gen, gen);
         lds_fence();
@@ -2035,7 +2045,7 @@ __device__ void pipe_clock(const LaunchArgs &L, const ItemArgs &I, const PipeWg 
             }
             __asm__ volatile("" ::: "memory");
         }
-        const bool restart = pending && bl == sw;
+        const bool restart = pending && b == sw;
         if (restart) {
             t = in_mask(hold) ? t_hold : t;
             act |= hold;
@@ -2201,7 +2211,8 @@ __device__ void pipe_clock(const LaunchArgs &L, const ItemArgs &I, const PipeWg 
         put_words<B * NA>(slot + G::O_L, lane, tw);
         *(v4u *)(ctl->lanes + 4 * si) = (v4u){(u32)was, (u32)(was >> 32), restart ? 1u : 0u, 0u};
         if (__builtin_expect(!pending && changed, 0)) {
-            if ((i32)(ctl_ld(&ctl->done_s) - sw) > 0)
+            // the row wave's number: at most a ring behind this one
+            if (b - (u64)(bl - ctl_ld(&ctl->done_s)) > sw)
                 claim(b + W.nb);
         }
         si_next = si + 1u == W.nb ? 0u : si + 1u;
