@@ -76,7 +76,9 @@ typedef struct ssa_run ssa_run;
 /* One reaction's propensity law.
  *   kind == SSA_LAW_MASS_ACTION: k >= 0 is the rate constant; the reactant
  *     orders come from ssa_model_create's reactant_order row (total order
- *     0..4); the propensity is (k / prod_s o_s!) prod_s x_s (x_s-1)...(x_s-o_s+1).
+ *     0..4); the propensity is (k / prod_s o_s!) prod_s x_s (x_s-1)...(x_s-o_s+1),
+ *     and zero where some x_s is below o_s. (A reaction may take more of a species
+ *     than its order in it, and so leave a count below zero.)
  *   kind == SSA_LAW_HILL_*: k = vmax >= 0, basal >= 0, K > 0, 1 <= h <= 8,
  *     0 <= regulator < n_species. */
 typedef struct ssa_law {

@@ -289,15 +289,29 @@ std::string gen_model(const Model &md, int idx, uint64_t record_mask)
     int lo_max = 0;
     for (int s = 0; s < md.N; ++s)
         lo_max = std::max(lo_max, lo[(size_t)s]);
+    // A reaction that takes more of a species than its order in it asks for (a loss of
+    // order zero, a Hill law's) can leave a count below zero, where a mass-action reaction
+    // of that species has propensity zero and only a guard gives it, and a Hill law takes
+    // the negative count, so that partial sums may fall.
+    std::vector<bool> negative((size_t)md.N, false);
+    for (int j = 0; j < md.M; ++j)
+        for (int s = 0; s < md.N; ++s)
+            if (md.nu[(size_t)j * md.N + s] < -md.order[(size_t)j * md.N + s])
+                negative[(size_t)s] = true;
     int d_max = 0;
-    bool multi = false;   // some mass-action reaction takes two species
+    bool multi = false;      // some mass-action reaction takes two species
+    bool below_zero = false; // some takes one whose count can be negative
+    bool careful = false;    // a Hill law's regulator can be
     for (int j = 0; j < md.M; ++j) {
         int reactants = 0;
         for (int s = 0; s < md.N; ++s) {
+            const bool takes = md.order[(size_t)j * md.N + s] > 0;
             d_max = std::max(d_max, (int)md.nu[(size_t)j * md.N + s]);
-            reactants += md.order[(size_t)j * md.N + s] > 0;
+            reactants += takes;
+            below_zero = below_zero || (takes && negative[(size_t)s]);
         }
         multi = multi || (md.law[j].kind == SSA_LAW_MASS_ACTION && reactants > 1);
+        careful = careful || (md.law[j].kind != SSA_LAW_MASS_ACTION && negative[(size_t)md.law[j].regulator]);
     }
     std::ostringstream o;
     o << "struct Md" << idx << " {\n"
@@ -306,12 +320,15 @@ std::string gen_model(const Model &md, int idx, uint64_t record_mask)
       << "  static constexpr u64 REC = " << record_mask << "ull;  // reactions whose firings are recorded\n"
       << "  static constexpr int LO_MAX = " << lo_max << ";  // largest reactant order of a species\n"
       << "  static constexpr int DMAX = " << d_max << ";  // largest increase of a count by one event\n"
-      << "  // zero guards outside the careful loop: a factor before the zero one may overflow fp16\n"
-      << "  template <class P> static constexpr bool needs_guard() { return P::NARROW && "
-      << (multi ? "true" : "false") << "; }\n"
-      << "  // some count below its species' largest reactant order (a zero guard may apply);\n"
-      << "  // counts are never negative, so x - lo < 0 exactly when x < lo, and the OR of\n"
-      << "  // the differences is negative when one of them is (one compare for the wave)\n"
+      << "  // zero guards outside the careful loop: a factor before the zero one may overflow\n"
+      << "  // fp16, or a reactant's count may be negative\n"
+      << "  template <class P> static constexpr bool needs_guard() { return "
+      << (below_zero ? "true" : multi ? "P::NARROW" : "false") << "; }\n"
+      << "  // a Hill law may meet a negative count: every batch is a careful one\n"
+      << "  static constexpr bool CAREFUL = " << (careful ? "true" : "false") << ";\n"
+      << "  // some count below its species' largest reactant order (a zero guard may apply):\n"
+      << "  // x - lo < 0 exactly when x < lo, and the OR of the differences is negative when\n"
+      << "  // one of them is (one compare for the wave)\n"
       << "  __device__ static __forceinline__ bool below(const i32 (&x)[N]) {\n"
       << "    (void)x;\n"
       << "    return (0";

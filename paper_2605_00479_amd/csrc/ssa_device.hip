@@ -767,8 +767,8 @@ struct Versions {
         return mx;
     }
 
-    // counts are never negative; as unsigned, a negative one would only send
-    // the wave to the version that handles every count
+    // as unsigned, a negative count (a network may allow one) only sends the wave
+    // to a version that handles every count
     __device__ static __forceinline__ int of(const i32 (&x)[Md::N], u64 act)
     {
         if constexpr (CONV) {
@@ -1718,7 +1718,7 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
         // The batch in straight line. KIND 0: every count within the exact-integer
         // limit; 1: conversions round, with the fields that came with the draws; 2:
         // every case (zero guards, conversion fields formed here, a target at or
-        // above the total), from the state before the batch.
+        // above the total, partial sums that fall), from the state before the batch.
         auto batch = [&](auto kind) __attribute__((always_inline)) {
             constexpr int KIND = decltype(kind)::value;
             __asm__ volatile("; kind %0" ::"i"(KIND));   // (keeps the kinds' common loads in each)
@@ -1762,7 +1762,7 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
                 } else {
                     u2 = value_at<A>(uw, e);
                 }
-                if (KIND != 2 && e == B / 2) {
+                if ((KIND != 2 || Md::CAREFUL) && e == B / 2) {
                     // the last batch's words have long been written: publish it, and ask
                     // for the next one's state
                     __asm__ volatile("" : "+v"(x[0]));   // not before this event
@@ -1770,7 +1770,7 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
                     lds_st(&ctl->done_e, b);
                     r2 = lds_ld(ctl->ready + si2);
                 }
-                if (KIND != 2 && e == B - 1) {
+                if ((KIND != 2 || Md::CAREFUL) && e == B - 1) {
                     __asm__ volatile("" : "+v"(r2), "+v"(x[0]));   // not before this event
                     acquire(b + 1u, si2, r2);
                 }
@@ -1814,8 +1814,8 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
                     target = PE::arnd(f32_kept(u2 * a0), pool.hw(S::TARGET));
                 else
                     target = u2 * a0;
-                // past[j]: the reaction comes after j (partial sums never fall, so the
-                // first false one names it). A target rounded up to the total selects the
+                // past[j]: the reaction comes after j (partial sums never fall outside KIND 2,
+                // so the first false one names it). A target rounded up to the total selects the
                 // last reaction that can fire: the last of all, where that one can (a
                 // 16-bit target is one in most bfloat16 batches and a fifth of the fp16
                 // ones of 64 lanes and 8 events); else the batch is computed again.
@@ -1864,7 +1864,10 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
                 conv_now = cv && conv_made;
             }
         }
-        if constexpr (G::CONV) {
+        if constexpr (Md::CAREFUL) {
+            batch(IC<2>());
+            again = 0;
+        } else if constexpr (G::CONV) {
             if (conv_now)
                 batch(IC<1>());
             else
@@ -1875,7 +1878,8 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
         if (__builtin_expect(((again & live) | over) != 0, 0)) {
             if (!more)
                 return;
-            batch(IC<2>());
+            if constexpr (!Md::CAREFUL)
+                batch(IC<2>());
         }
         put_words<B * NA>(slot + G::O_A, lane, aw);
         if constexpr (P::NORM)
