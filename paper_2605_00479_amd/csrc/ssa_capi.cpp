@@ -514,13 +514,14 @@ std::string gen_source(const std::vector<const Model *> &models, const ModeSpec 
     int m_max = 0;
     for (size_t i = 0; i < models.size(); ++i)
         m_max = std::max(m_max, models[i]->M);
-    // pipelined event loop: one workgroup to a CU (ssa_kernel_pl) and two (ssa_kernel_ph)
+    // pipelined event loop: one workgroup to a CU (ssa_kernel_pl) and two (ssa_kernel_ph). Above
+    // 16 reactions a wave has up to 256 registers and a SIMD two waves: one workgroup to a CU
     for (int half = 0; half < 2; ++half) {
         const std::string h = half ? "true" : "false";
         o << "extern \"C\" __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu("
           << (m_max <= 16 ? "4, 4" : "2, 2") << ")))\n"
           << (half ? "ssa_kernel_ph" : "ssa_kernel_pl") << "(LaunchArgs L) {\n"
-          << "  if constexpr (true";
+          << "  if constexpr (" << (half && m_max > 16 ? "false" : "true");
         for (size_t i = 0; i < models.size(); ++i)
             o << " && PipeGeom<PrecRun, Md" << i << ", " << h << ">::OK";
         o << ") {\n"
@@ -1137,6 +1138,12 @@ int build_source(const ssa_run_desc *d, std::string &src)
 }  // namespace
 
 // ------------------------------------------------------------------ run object
+// The parameter sets of an item, by the event rates at the start.
+struct Rates {
+    double mean = 0.0;
+    double spread = 1.0;   // the largest over the mean
+};
+
 struct ItemBuf {
     int N = 0, M = 0;
     int64_t E = 0;
@@ -1162,6 +1169,7 @@ struct ItemBuf {
     uint32_t traj_per_set = 0;
     uint32_t id_base = 0;
     double pace = 0.0;           // event rate at the start times the work of an event
+    Rates start;
 };
 
 struct ssa_run {
@@ -1462,6 +1470,86 @@ int dispatch_launch(ssa_run *r, const ssa_run_desc *d, const Loaded &ld, int n_c
     }
 }
 
+Rates start_rates(const ssa_item &it)
+{
+    const Model &md = it.model->m;
+    std::vector<double> base(md.M), slope(md.M);   // propensities are linear in the constant
+    for (int j = 0; j < md.M; ++j) {
+        base[j] = propensity(md, j, 0.0, it.x0);
+        slope[j] = propensity(md, j, 1.0, it.x0) - base[j];
+    }
+    // (sets that no trajectory uses are left out)
+    const int64_t sets = !it.set_rates ? 1 : it.n_sets == 1 ? 1
+                       : std::min<int64_t>(it.n_sets, (it.n_traj + it.traj_per_set - 1) / it.traj_per_set);
+    Rates r;
+    double most = 0.0;
+    for (int64_t i = 0; i < sets; ++i) {
+        double a = 0.0;
+        for (int j = 0; j < md.M; ++j)
+            a += base[j] + slope[j] * (it.set_rates ? it.set_rates[i * md.M + j] : md.law[j].k);
+        r.mean += a / (double)sets;
+        most = std::max(most, a);
+    }
+    if (r.mean > 0.0 && std::isfinite(most / r.mean))
+        r.spread = most / r.mean;
+    return r;
+}
+
+// Workgroups up to which each of the pipelined kernel's has a CU to itself. A chain of
+// events is fastest there; beyond, two share a CU where its SIMDs would idle otherwise: the
+// event wave of a 16-bit mode is the slower part (dimer, many full waves: 293 cycles per 64
+// events of a CU alone, 180 in two; 1M telegraph trajectories 44.1 and 28.1 ms), in FP64
+// the draws are, which keep the SIMDs busier (198 alone, 161 in two). Alone is better
+// where the ends are long and ragged, each lane then having half as many waves beside it:
+// FP64 in the first two rounds (Schloegl, 33,000: 1.8 and 2.2 ms), and sweeps or several
+// networks, whose chains differ most, in the first eight (64k-trajectory dimer sweep 26.7
+// and 46.8 ms, five networks of 20k 107.6 and 111.2; dimer MIX_F16_SR at 12 rounds 2.13 and
+// 2.21, telegraph sweep 0.33 and 0.26).
+int64_t pipe_alone(const ssa_run_desc *d, int cus)
+{
+    const bool mixed = d->n_items > 1 || (d->items[0].set_rates && d->items[0].n_sets > 1);
+    return (mixed ? 8 : d->format == SSA_FMT_FP64 ? 2 : 1) * (int64_t)cus;
+}
+
+// Whether so many workgroups of 64 trajectories are better run by one wave each
+// (ssa_kernel). Its chain of events takes 1.4 to 2.6 times as long, but a CU holds four to
+// twelve of them. Networks of equal parts (births, first-order, bimolecular and pair losses)
+// of so many reactions, milliseconds pipelined and by one wave; a round is a workgroup to a CU:
+//   more than 16 reactions (one workgroup to a CU whatever the ensemble's size):
+//     24: FP64 2 rounds 0.76 and 0.77, 4 1.38 and 0.80; MIX_F16_SR 2 1.14 and 0.96, 4 2.2 and 1.0
+//     32: FP64 1 round 0.57 and 0.92, 2 1.09 and 0.93; MIX_F16_SR 2 1.57 and 1.13, 16 11.3 and 4.5;
+//         sets of spread 2.6, 2 rounds: the pipelined kernel 1.2 to 1.4 times faster
+//     64: FP64 1 round 1.69 and 1.75, 2 3.2 and 1.8, 16 23.5 and 7.0
+//   13 to 16, binary32 and 16-bit modes (FP64 stays within 10% either way):
+//     16: MIX_F16_SR 2 rounds 3.0 and 4.1, 2.5 5.6 and 4.1, 8 11.4 and 7.0 (sets of spread 2.6:
+//         7.5 and 8.5)
+//   5 to 12, the same modes: trajectories of one length would ask for one wave from about 8
+//   rounds on, ragged ones (repressilator, MIX_F16_SR: 12 rounds 20.8 and 27.4, 23 34.4 and
+//   37.0, 35 47.7 and 44.2) from 25:
+//     12: MIX_F16_SR 8 rounds 8.0 and 4.9, 16 16.0 and 9.0
+//      8: MIX_F16_SR 8 rounds 4.5 and 3.3, 16 8.9 and 6.1
+//   up to 4 the networks measured stay within 20% either way.
+//   Short trajectories, more of them than lanes (8 rounds): the one-wave kernel's lanes leave
+//   the loop for each claim: 16 reactions, 390 events, MIX_F16_SR 32 rounds 3.8 and 4.8 (the
+//   loop's advantage makes up for it from about 2,500 events on)
+bool one_wave_better(const ssa_run_desc *d, const Rates &start, int cus, int64_t wgs)
+{
+    int M = 0;
+    for (int i = 0; i < d->n_items; ++i)
+        M = std::max(M, d->items[i].model->m.M);
+    const bool wide = d->format == SSA_FMT_FP64;
+    const double rounds = (double)wgs / cus;
+    const bool ragged = d->n_items > 1 || start.spread >= 2.0;
+    if (M > 16)
+        return rounds > ((wide && M <= 24) || (ragged && M <= 32) ? 2.0 : 1.0);
+    if (wide || ragged || M <= 4)
+        return false;
+    // (events are about twice this where counts grow from the start)
+    if (start.mean * d->t_end >= 1000.0)
+        return rounds > (M > 12 ? 2.0 : 12.0);
+    return M > 12 && rounds > 2.0 && rounds <= 8.0;
+}
+
 int run_impl(const ssa_run_desc *d, ssa_run *r)
 {
     HIP_TRY(hipGetDevice(&r->device));
@@ -1553,6 +1641,7 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
         // repressilator 752 at twelve)
         for (int j = 0; j < md.M; ++j)
             b.pace += propensity(md, j, it.set_rates ? it.set_rates[j] : md.law[j].k, it.x0) * (md.M + 1);
+        b.start = start_rates(it);
         std::vector<char> htab((size_t)2 * md.M * tsz);
         char *ht = htab.data();
         for (int j = 0; j < md.M; ++j) {
@@ -1626,31 +1715,26 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
     // launch shape: enough waves to cover the ensemble, at most what stays resident
     const int cus = ld.cus;
     r->block = d->block_size ? d->block_size : (have_tuned ? tuned.block : 512);
-    bool mixed = d->n_items > 1;   // chains of unequal length
-    for (int i = 0; i < d->n_items; ++i)
-        mixed |= d->items[i].set_rates && d->items[i].n_sets > 1;
     const int asked = d->grid_size ? d->grid_size : (have_tuned && tuned.block == r->block ? tuned.grid : 0);
-    // 512: the pipelined kernel, which also is the default; a network whose ring does
-    // not fit a CU's LDS runs one wave per 64 trajectories throughout
-    r->pipe = r->block == 512 && ld.pl_ok;
+    // 512: the pipelined kernel. A workgroup runs 64 trajectories at a time; a grid size
+    // asked for counts 256. One wave per 64 trajectories runs instead where its batches do
+    // not fit a CU's LDS, where its event wave would keep two registers for each of more
+    // than 32 constants a lane (64 reactions, FP64: 273 spilled, 6.6 ms and 2.05; 48: 2.2
+    // and 1.5), and by default where it is the better one.
+    bool sets = false;
+    int m_max = 0;
+    for (int i = 0; i < d->n_items; ++i) {
+        sets |= d->items[i].set_rates && d->items[i].n_sets > 1;
+        m_max = std::max(m_max, d->items[i].model->m.M);
+    }
+    int64_t wgs = std::max<int64_t>(1, (total + 63) / 64);
+    if (asked)
+        wgs = std::min<int64_t>(wgs, 4 * (int64_t)asked);
+    const bool chosen = d->block_size == 512 || have_tuned;
+    r->pipe = r->block == 512 && ld.pl_ok && !(wide && sets && m_max > 32) &&
+              (chosen || !one_wave_better(d, r->items[0].start, cus, wgs));
     if (r->pipe) {
-        // A workgroup runs 64 trajectories at a time; a grid size asked for counts 256.
-        // Up to one workgroup per CU each has a CU to itself, where a chain of events is
-        // fastest. Beyond that two share a CU if its SIMDs would idle otherwise: the
-        // event wave of a 16-bit mode is the slower part (dimer, many full waves: 293
-        // cycles per 64 events of a CU alone, 180 in two; 1M telegraph trajectories 44.1
-        // and 28.1 ms), in FP64 the draws are, which keep the SIMDs busier (198 alone, 161
-        // in two). Alone is better where the ends are long and ragged, each lane then
-        // having half as many waves beside it: FP64 in the first two rounds (Schloegl,
-        // 33,000: 1.8 and 2.2 ms), and sweeps or several networks, whose chains differ
-        // most, in the first eight (64k-trajectory dimer sweep 26.7 and 46.8 ms, five
-        // networks of 20k 107.6 and 111.2; dimer MIX_F16_SR at 12 rounds 2.13 and 2.21,
-        // telegraph sweep 0.33 and 0.26).
-        int64_t wgs = std::max<int64_t>(1, (total + 63) / 64);
-        if (asked)
-            wgs = std::min<int64_t>(wgs, 4 * (int64_t)asked);
-        const int64_t rounds_alone = asked ? 1 : mixed ? 8 : wide ? 2 : 1;
-        r->pipe_two = ld.ph_ok && wgs > rounds_alone * cus;
+        r->pipe_two = ld.ph_ok && wgs > (asked ? cus : pipe_alone(d, cus));
         r->grid = (int)std::min<int64_t>(wgs, r->pipe_two ? 2 * (int64_t)cus : cus);
         r->vgprs = r->pipe_two ? ld.vgprs_ph : ld.vgprs_pl;
     } else {
