@@ -1501,14 +1501,24 @@ Rates start_rates(const ssa_item &it)
 // events of a CU alone, 180 in two; 1M telegraph trajectories 44.1 and 28.1 ms), in FP64
 // the draws are, which keep the SIMDs busier (198 alone, 161 in two). Alone is better
 // where the ends are long and ragged, each lane then having half as many waves beside it:
-// FP64 in the first two rounds (Schloegl, 33,000: 1.8 and 2.2 ms), and sweeps or several
-// networks, whose chains differ most, in the first eight (64k-trajectory dimer sweep 26.7
-// and 46.8 ms, five networks of 20k 107.6 and 111.2; dimer MIX_F16_SR at 12 rounds 2.13 and
-// 2.21, telegraph sweep 0.33 and 0.26).
-int64_t pipe_alone(const ssa_run_desc *d, int cus)
+// FP64 in the first two rounds (Schloegl, 33,000: 1.8 and 2.2 ms), several networks in the
+// first eight (five networks of 20k 107.6 and 111.2). In a sweep the spread of its sets
+// decides, by their rates at the start (the largest over the mean), alone and in two:
+//   dimer sweep, 4.6:      FP64 12 rounds 6.2 and 8.3 ms, MIX_F16_SR 8 rounds 5.4 and 5.5
+//   4 reactions, 2.6:      FP64 6 rounds 1.54 and 1.57, MIX_F16_SR 2 0.94 and 0.98, 3 1.25 and 1.08
+//   4 reactions, 1.3:      FP64 4 rounds 2.1 and 2.3, MIX_F16_SR 1.2 1.45 and 1.25, 8 5.8 and 4.1
+//   12 reactions, 1.3:     FP64 2 rounds 2.7 and 1.9, 8 9.6 and 6.5
+//   telegraph sweep, 1.0:  FP64 3.1 rounds 0.24 and 0.27, 5.5 0.31 and 0.28; UNI_F16_SR 7 0.28 and 0.26
+int64_t pipe_alone(const ssa_run_desc *d, const Rates &start, int cus)
 {
-    const bool mixed = d->n_items > 1 || (d->items[0].set_rates && d->items[0].n_sets > 1);
-    return (mixed ? 8 : d->format == SSA_FMT_FP64 ? 2 : 1) * (int64_t)cus;
+    const bool wide = d->format == SSA_FMT_FP64;
+    if (d->n_items > 1)
+        return 8 * (int64_t)cus;
+    if (!d->items[0].set_rates || d->items[0].n_sets < 2)
+        return (wide ? 2 : 1) * (int64_t)cus;
+    const double rounds = start.spread * start.spread * (wide ? 2.0 : 0.5);
+    const double least = wide && d->items[0].model->m.M <= 4 ? 4.0 : 2.0;
+    return (int64_t)(std::min(8.0, std::max(least, rounds)) * cus);
 }
 
 // Whether so many workgroups of 64 trajectories are better run by one wave each
@@ -1734,7 +1744,7 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
     r->pipe = r->block == 512 && ld.pl_ok && !(wide && sets && m_max > 32) &&
               (chosen || !one_wave_better(d, r->items[0].start, cus, wgs));
     if (r->pipe) {
-        r->pipe_two = ld.ph_ok && wgs > (asked ? cus : pipe_alone(d, cus));
+        r->pipe_two = ld.ph_ok && wgs > (asked ? cus : pipe_alone(d, r->items[0].start, cus));
         r->grid = (int)std::min<int64_t>(wgs, r->pipe_two ? 2 * (int64_t)cus : cus);
         r->vgprs = r->pipe_two ? ld.vgprs_ph : ld.vgprs_pl;
     } else {

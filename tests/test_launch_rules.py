@@ -77,6 +77,18 @@ def sweep(reactions, factors):
     return np.asarray(spec.rate)[None, :] * np.asarray(factors)[:, None]
 
 
+@pytest.mark.parametrize("mode,factors,alone", [
+    ("FP64", np.geomspace(0.01, 1.0, 64), 8),     # spread 4.4
+    ("MIX_F16_SR", np.geomspace(0.01, 1.0, 64), 8),
+    ("FP64", np.linspace(0.7, 1.3, 64), 4), ("MIX_F16_SR", np.linspace(0.7, 1.3, 64), 2),
+    ("FP64", np.ones(9), 4), ("UNI_F16_SR", np.ones(9), 2),
+])
+def test_sweeps_have_cus_to_themselves_by_their_spread(lib, mode, factors, alone):
+    for rounds, kernel in ((alone, PL), (alone + 0.1, PH)):
+        n = 64 * int(rounds * CUS)
+        assert shape(lib, [item(parts(4), n, sweep(4, factors))], mode)[0] == kernel
+
+
 def test_sweeps_of_many_reactions(lib):
     lib.fake_set(b"ph_lds", 0)
     wide_range = np.geomspace(0.05, 1.0, 32)
