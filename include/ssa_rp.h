@@ -264,7 +264,10 @@ int ssa_ensemble_run(const ssa_run_desc *desc, ssa_run **out);
  *   - snapshot windows are always launched directly (no graph), and no run
  *     handle, events or timings are made: the work is queued on
  *     desc->hip_stream (tables copied asynchronously on it) and the results
- *     are in the caller's buffers once that stream has passed it.
+ *     are in the caller's buffers once that stream has passed it;
+ *   - while hip_stream captures a graph, the tables go into the graph with the
+ *     launches: the inputs may be freed after the call, and the graph may be
+ *     replayed (serialised with other calls, below) as long as the outputs live.
  * Every call on one device shares that device's array: calls whose work may
  * overlap on a device (other streams, other threads) race and must be
  * serialised by the caller. Allocates no device memory and calls no device

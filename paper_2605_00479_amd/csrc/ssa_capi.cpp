@@ -474,6 +474,12 @@ std::string gen_model(const Model &md, int idx, uint64_t record_mask)
     return o.str();
 }
 
+// Words that a launch of ssa_upload carries in its arguments (they stay below 4 KB).
+constexpr int kUploadWords = 896;
+struct UploadH {
+    uint32_t w[kUploadWords];
+};
+
 struct ModeSpec {
     int fmt, accum, rnd, norm;
     std::string policy() const
@@ -561,6 +567,10 @@ std::string gen_source(const std::vector<const Model *> &models, const ModeSpec 
     o << "extern \"C\" __global__ void ssa_fill_u32(u32 *p, u32 n, u32 v) {\n"
       << "  u32 i = blockIdx.x * blockDim.x + threadIdx.x;\n"
       << "  if (i < n) p[i] = v;\n"
+      << "}\n"
+      << "struct Upload { u32 w[" << kUploadWords << "]; };\n"
+      << "extern \"C\" __global__ void ssa_upload(u32 *p, u32 n, Upload a) {\n"
+      << "  for (u32 i = threadIdx.x; i < n; i += blockDim.x) p[i] = a.w[i];\n"
       << "}\n";
     return o.str();
 }
@@ -774,7 +784,7 @@ struct Loaded {
     // ring fits, and as many are resident)
     hipFunction_t kernel_pl = nullptr, kernel_ph = nullptr;
     bool pl_ok = false, ph_ok = false;
-    hipFunction_t fill = nullptr;
+    hipFunction_t fill = nullptr, upload = nullptr;
     hipFunction_t rg_hist = nullptr, rg_scan = nullptr, rg_scatter = nullptr;
     int vgprs = -1, vgprs_pl = -1, vgprs_ph = -1;
     int cus = 0;
@@ -843,6 +853,7 @@ int get_kernel(const ssa_run_desc *d, const SourceId &id, Loaded &out, bool load
     HIP_TRY(hipModuleGetFunction(&ld.kernel_pl, ld.mod, "ssa_kernel_pl"));
     HIP_TRY(hipModuleGetFunction(&ld.kernel_ph, ld.mod, "ssa_kernel_ph"));
     HIP_TRY(hipModuleGetFunction(&ld.fill, ld.mod, "ssa_fill_u32"));
+    HIP_TRY(hipModuleGetFunction(&ld.upload, ld.mod, "ssa_upload"));
     HIP_TRY(hipModuleGetFunction(&ld.rg_hist, ld.mod, "ssa_regroup_hist"));
     HIP_TRY(hipModuleGetFunction(&ld.rg_scan, ld.mod, "ssa_regroup_scan"));
     HIP_TRY(hipModuleGetFunction(&ld.rg_scatter, ld.mod, "ssa_regroup_scatter"));
@@ -1560,19 +1571,35 @@ bool one_wave_better(const ssa_run_desc *d, const Rates &start, int cus, int64_t
     return M > 12 && rounds > 2.0 && rounds <= 8.0;
 }
 
+// The tables of a run whose stream is capturing. The host copy lives until the call
+// returns, and a captured copy of it would be replayed from freed memory: the bytes go
+// with the launches of a kernel instead, whose arguments the graph keeps. (About 3 us a
+// launch of 3.5 KB: a sweep of 4,096 sets of four constants, 131 KB, takes 38.)
+int upload_captured(ssa_run *r, const Loaded &ld, char *base, const std::vector<char> &bytes)
+{
+    UploadH u;
+    for (size_t off = 0; off < bytes.size(); off += sizeof u) {
+        const size_t n = std::min(sizeof u, bytes.size() - off);
+        std::memset(&u, 0, sizeof u);
+        std::memcpy(&u, bytes.data() + off, n);
+        void *p = base + off;
+        uint32_t words = (uint32_t)(n / 4);   // every table is of 4- or 8-byte values
+        void *args[] = {&p, &words, &u};
+        HIP_TRY(hipModuleLaunchKernel(ld.upload, 1, 1, 1, 256, 1, 1, 0, r->stream, args, nullptr));
+    }
+    return SSA_OK;
+}
+
 int run_impl(const ssa_run_desc *d, ssa_run *r)
 {
     HIP_TRY(hipGetDevice(&r->device));
     r->stream = (hipStream_t)d->hip_stream;
     r->K = d->n_snap;
-    if (!r->noalloc) {
-        // the tables' host copy lives until this call returns: a captured copy of it
-        // would be replayed from freed memory
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        HIP_TRY(hipStreamIsCapturing(r->stream, &cap));
-        if (cap != hipStreamCaptureStatusNone)
-            return fail(SSA_E_DEVICE, "ssa_ensemble_run cannot be captured into a graph: its stream is capturing");
-    }
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(r->stream, &cap));
+    const bool capturing = cap != hipStreamCaptureStatusNone;
+    if (capturing && !r->noalloc)
+        return fail(SSA_E_DEVICE, "ssa_ensemble_run cannot be captured into a graph: its stream is capturing");
     const SourceId id = source_id(d);
     Loaded ld;
     int rc = get_kernel(d, id, ld, !r->noalloc);
@@ -1711,8 +1738,12 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
             return rc;
         // ordered on the run's stream, after earlier work there (from pageable memory, the
         // call returns once the bytes have been taken)
-        if (!blob.empty())
+        if (capturing) {
+            if ((rc = upload_captured(r, ld, base, blob)))
+                return rc;
+        } else if (!blob.empty()) {
             HIP_TRY(hipMemcpyAsync(base, blob.data(), blob.size(), hipMemcpyHostToDevice, r->stream));
+        }
         r->t64 = (double *)(base + off_t64);
         r->t32 = (float *)(base + off_t32);
         for (int i = 0; i < d->n_items; ++i) {

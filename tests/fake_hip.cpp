@@ -16,6 +16,7 @@ std::ostringstream g_log;
 std::map<std::string, long> g_set;
 std::string g_text;
 long g_events = 0;
+void *g_tables = nullptr;   // where the last copy or first upload since it was taken went
 
 long setting(const char *name, long otherwise)
 {
@@ -41,6 +42,12 @@ const char *fake_log()
 {
     g_text = g_log.str();
     return g_text.c_str();
+}
+
+void *fake_tables()
+{
+    void *p = g_tables;
+    return g_tables = nullptr, p;
 }
 
 hipError_t hipGetDevice(int *d) { return *d = 0, hipSuccess; }
@@ -74,8 +81,11 @@ hipError_t hipModuleLaunchKernel(hipFunction_t f, unsigned gx, unsigned, unsigne
 {
     const std::string name = name_of(f);
     g_log << "launch " << name << " " << gx << " " << bx << " " << lds << "\n";
-    if (name == "ssa_upload")
+    if (name == "ssa_upload") {
+        if (!g_tables)
+            g_tables = *(void **)args[0];
         std::memcpy(*(void **)args[0], args[2], 4 * (size_t) * (unsigned *)args[1]);
+    }
     return hipSuccess;
 }
 
@@ -96,8 +106,10 @@ hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind)
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t)
 {
     g_log << "memcpy_async " << n << "\n";
-    if (!setting("capturing", 0))   // (a captured copy happens when the graph is launched)
+    if (!setting("capturing", 0)) {   // (a captured copy happens when the graph is launched)
+        g_tables = d;
         std::memcpy(d, s, n);
+    }
     return hipSuccess;
 }
 

@@ -20,7 +20,7 @@ def load(folder, monkeypatch):
     so = os.path.join(folder, "libssa_host.so")
     if not os.path.exists(so):
         subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-w", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__",
-                        "-D__align__(n)=", "-DHIP_SYMBOL(x)=(&x)", "-I", os.path.join(rocm, "include"),
+                        "-D__align__(n)=", "-DHIP_SYMBOL(x)=x", "-I", os.path.join(rocm, "include"),
                         "-I", os.path.join(build.ROOT, "include"), "-I", build.BUILD,
                         os.path.join(build.HERE, "ssa_capi.cpp"), os.path.join(HERE, "fake_hip.cpp"), "-o", so, "-ldl"],
                        check=True)
@@ -36,6 +36,7 @@ def load(folder, monkeypatch):
     lib = ssa.lib()
     assert real != so
     lib.fake_log.restype = ctypes.c_char_p
+    lib.fake_tables.restype = ctypes.c_void_p
     lib.fake_set.argtypes = [ctypes.c_char_p, ctypes.c_long]
     lib.fake_reset()
     return lib
