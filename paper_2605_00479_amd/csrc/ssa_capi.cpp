@@ -1738,6 +1738,7 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
             return rc;
         // ordered on the run's stream, after earlier work there (from pageable memory, the
         // call returns once the bytes have been taken)
+        r->queued = true;   // (a refusal from here on waits for the stream)
         if (capturing) {
             if ((rc = upload_captured(r, ld, base, blob)))
                 return rc;
@@ -1803,7 +1804,6 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
     r->n_launch = n_chunks;
     if (r->noalloc) {   // direct launches, no events
         r->graph = false;
-        r->queued = true;
         return dispatch_launch(r, d, ld, n_chunks);
     }
     if ((rc = event_take(r->device, &r->ev0)) || (rc = event_take(r->device, &r->ev1)))
@@ -1818,7 +1818,6 @@ int run_impl(const ssa_run_desc *d, ssa_run *r)
                 return rc;
     }
     HIP_TRY(hipEventRecord(r->ev0, r->stream));
-    r->queued = true;
     if (r->graph) {
         HIP_TRY(hipStreamCreateWithFlags(&r->cap, hipStreamNonBlocking));
         HIP_TRY(hipStreamBeginCapture(r->cap, hipStreamCaptureModeThreadLocal));
