@@ -197,7 +197,8 @@ def kernel_name(info):
     if info["block_size"] != 512:
         return "ssa_kernel"
     cus = torch.cuda.get_device_properties(torch.cuda.current_device()).multi_processor_count
-    return "ssa_kernel_ph" if info["grid_size"] > cus else "ssa_kernel_pl"
+    # (a grid of 512-thread workgroups counts four pipelined ones each)
+    return "ssa_kernel_ph" if 4 * info["grid_size"] > cus else "ssa_kernel_pl"
 
 
 def physical_cores():

@@ -169,16 +169,19 @@ typedef struct ssa_item {
  *     launch. 0 = the autotuned choice for this kernel and workload shape if
  *     ssa_autotune stored one, else 1.
  *   block_size, grid_size: launch shape; 0 = the autotuned choice if stored,
- *     else 512 threads and workgroups for one trajectory per lane (up to what
- *     stays resident). block_size a multiple of 64 up to 256: every wave runs 64
- *     trajectories. 512: the pipelined kernel, where the eight waves of a workgroup
- *     run the events of 64 trajectories together (draws, events, clock and rows in
- *     waves of their own, passing batches through LDS); a grid_size counts 256
- *     trajectories a workgroup there too, so four workgroups are launched for each
- *     (up to two per CU). A network whose batches do not fit a CU's LDS runs on
- *     256 threads. Results are bit-identical in every shape: the draws are the
- *     same function of seed, trajectory and event index. ssa_run_info reports
- *     the shape launched.
+ *     else a choice by the networks, the ensemble's size and the precision, and
+ *     workgroups for one trajectory per lane (up to what stays resident).
+ *     block_size a multiple of 64 up to 256: every wave runs 64 trajectories.
+ *     512: the pipelined kernel, where the eight waves of a workgroup run the events
+ *     of 64 trajectories together (draws, events, clock and rows in waves of their
+ *     own, passing batches through LDS); a grid_size counts 256 trajectories a
+ *     workgroup there too, so four workgroups are launched for each (up to two per
+ *     CU). A network whose batches do not fit a CU's LDS, or a sweep of more than 32
+ *     reactions in FP64, runs on 256 threads. Large ensembles of networks of more
+ *     than 16 reactions are faster on 256 threads, which 0 chooses. Results are
+ *     bit-identical in every shape: the draws are the same function of seed,
+ *     trajectory and event index. ssa_run_info reports the shape launched, in
+ *     these units.
  *   reorder: chunked runs only. 0 or 1: before each chunk after the first,
  *     trajectories are claimed in order of the events they fired in the
  *     previous chunk, heaviest first (results are unchanged: draws are keyed
@@ -302,7 +305,7 @@ typedef struct ssa_run_info {
     double kernel_ms;         /* sum of the simulation kernels' own durations */
     int32_t n_launches;       /* simulation kernel launches (chunks) */
     int32_t block_size;
-    int32_t grid_size;
+    int32_t grid_size;        /* as a request for it would be (512 threads: 256 trajectories each) */
     int32_t vgprs;            /* not known: -1 */
     uint64_t total_events;    /* sum of events over all trajectories */
     int32_t first_window;     /* snapshot rows of the first launch (0: even windows) */

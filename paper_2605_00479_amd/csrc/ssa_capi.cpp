@@ -2109,7 +2109,8 @@ int ssa_run_info_get(const ssa_run *run, ssa_run_info *info)
     info->kernel_ms = kms;
     info->n_launches = run->n_launch;
     info->block_size = run->block;
-    info->grid_size = run->grid;
+    // in the unit of a request: of 512 threads, a workgroup for 256 trajectories
+    info->grid_size = run->pipe ? (run->grid + 3) / 4 : run->grid;
     info->vgprs = run->vgprs;
     uint64_t tot = 0;
     for (const ItemBuf &b : run->items) {
