@@ -270,9 +270,18 @@ std::string gen_propensities_packed(const Model &md)
     return o.str();
 }
 
+// Dynamic LDS of a workgroup of the pipelined kernels (ring and tables), two to a CU and
+// one: a CU's 160 KB without PipeCtl and the snapshot times (4.4 KB in binary64, 2.4 KB
+// else). Kernels are generated with it and launched with it.
+unsigned pipe_lds(int format, bool half)
+{
+    const bool wide = format == SSA_FMT_FP64;
+    return half ? (wide ? 75 * 1024 : 77 * 1024 + 512) : (wide ? 155 * 1024 : 157 * 1024);
+}
+
 // Device description of one network: propensity op sequence with its static
 // rounding slots (main and conversion), and the integer update x += nu_mu.
-std::string gen_model(const Model &md, int idx, uint64_t record_mask)
+std::string gen_model(const Model &md, int idx, uint64_t record_mask, int format)
 {
     int nprop = 0, nconv = 0;
     for (int j = 0; j < md.M; ++j) {
@@ -319,6 +328,9 @@ std::string gen_model(const Model &md, int idx, uint64_t record_mask)
       << "  static constexpr int N = " << md.N << ", M = " << md.M << ", NPROP = " << nprop << ", NCONV = " << nconv
       << ";\n"
       << "  static constexpr u64 REC = " << record_mask << "ull;  // reactions whose firings are recorded\n"
+      << "  // bytes of a pipelined workgroup's ring and tables, with two to a CU and with one\n"
+      << "  __host__ __device__ static constexpr int pipe_lds(bool half) { return half ? " << pipe_lds(format, true)
+      << " : " << pipe_lds(format, false) << "; }\n"
       << "  static constexpr int LO_MAX = " << lo_max << ";  // largest reactant order of a species\n"
       << "  static constexpr int DMAX = " << d_max << ";  // largest increase of a count by one event\n"
       << "  // zero guards outside the careful loop: a factor before the zero one may overflow\n"
@@ -502,7 +514,7 @@ std::string gen_source(const std::vector<const Model *> &models, const ModeSpec 
     std::ostringstream o;
     o << "#define SSA_N_ITEMS " << models.size() << "\n" << kDeviceSource << "\n";
     for (size_t i = 0; i < models.size(); ++i)
-        o << gen_model(*models[i], (int)i, record_masks[i]);
+        o << gen_model(*models[i], (int)i, record_masks[i], ms.fmt);
     o << "typedef " << ms.policy() << " PrecRun;\n"
       << "extern \"C\" __global__ void __launch_bounds__(256) ssa_kernel(LaunchArgs L) {\n"
       << "  const u32 wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;\n"
@@ -769,14 +781,6 @@ struct SourceId {
     uint64_t hash = 0;
     size_t size = 0;
 };
-
-// dynamic LDS of a workgroup of the pipelined kernels, two to a CU and one
-// (pipe_lds in ssa_device.hip)
-unsigned pipe_lds(int format, bool half)
-{
-    const bool wide = format == SSA_FMT_FP64;
-    return half ? (wide ? 75 * 1024 : 77 * 1024 + 512) : (wide ? 155 * 1024 : 157 * 1024);
-}
 
 struct Loaded {
     hipModule_t mod = nullptr;

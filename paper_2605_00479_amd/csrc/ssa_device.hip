@@ -1219,13 +1219,6 @@ typedef u32 v2u __attribute__((ext_vector_type(2)));
 
 constexpr int kPipeBatches = 16;   // most batches of a ring
 constexpr int kSnapTable = 512;    // snapshot times kept in LDS
-// bytes of ring and tables, with two workgroups to a CU and with one: a CU's 160 KB
-// without PipeCtl and the snapshot times (4.4 KB in binary64, 2.4 KB else)
-template <class P>
-constexpr int pipe_lds(bool half)
-{
-    return half ? (P::WIDE ? 75 * 1024 : 77 * 1024 + 512) : (P::WIDE ? 155 * 1024 : 157 * 1024);
-}
 
 struct __attribute__((aligned(16))) PipeCtl {
     u32 ready[kPipeBatches];
@@ -1341,9 +1334,9 @@ struct PipeGeom {
     static constexpr int pick()
     {
         for (int b = HALF ? 4 : Md::M <= 12 ? 8 : Md::M <= 32 ? 4 : 2; b >= 2; b /= 2)
-            if (fits(b, HALF ? 6 : 5, pipe_lds<P>(HALF)))
+            if (fits(b, HALF ? 6 : 5, Md::pipe_lds(HALF)))
                 return b;
-        return fits(2, 4, pipe_lds<P>(HALF)) ? 2 : 0;
+        return fits(2, 4, Md::pipe_lds(HALF)) ? 2 : 0;
     }
     static constexpr bool OK = pick() != 0;
     static constexpr int B = OK ? pick() : 2;

@@ -1,9 +1,11 @@
 """The kernel and grid that a run is given, without a GPU (fake_hip.cpp): which of the
 event loops, and one or two of its workgroups to a CU (256 CUs here)."""
+import re
+
 import numpy as np
 import pytest
 
-from paper_2605_00479_amd import workloads as wl
+from paper_2605_00479_amd import ssa, workloads as wl
 from host_library import item, launched, load, start
 
 CUS = 256
@@ -104,3 +106,17 @@ def test_several_networks(lib):
     assert shape(lib, its, "MIX_BF16_SR")[0] == PL
     its = [item(parts(12), 64 * 40 * CUS), item(parts(2), 64 * CUS)]
     assert shape(lib, its, "MIX_BF16_SR")[0] == PH
+
+
+@pytest.mark.parametrize("mode", ["FP64", "FP32", "UNI_BF16_SR"])
+def test_kernels_are_launched_with_the_lds_they_are_built_for(lib, tmp_path, mode):
+    # a ring of more batches than the launch has LDS for would be accessed out of range
+    sizes = {}
+    for wgs in (1, 4 * CUS):
+        its = [item(wl.birth_death(), 64 * wgs)]
+        rc, h, log = start(lib, its, mode)
+        lib.ssa_run_destroy(h)
+        sizes.update({line.split()[1]: int(line.split()[4]) for line in log if "ssa_kernel" in line})
+    ssa.ssa_dump_source(its, 1.0, [1.0], mode, tmp_path / "k.hip", max_events=1)
+    built = re.findall(r"pipe_lds\(bool half\) \{ return half \? (\d+) : (\d+);", (tmp_path / "k.hip").read_text())
+    assert [(sizes[PH], sizes[PL])] == [tuple(map(int, b)) for b in built]
