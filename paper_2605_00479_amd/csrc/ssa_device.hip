@@ -129,12 +129,13 @@ __device__ __forceinline__ float unif24(u32 w, const DrawConst &k = DrawConst())
 
 // --------------------------------------------------------------------------
 // Correctly rounded binary32 a / b (the IEEE quotient) for operands that need
-// no range scaling: a = 0 or 2^-26 <= |a| < 32, and 2^-24 <= b < 2^27. The
+// no range scaling: a = 0 or 2^-24 <= |a| < 32, and 2^-60 <= b < 2^60. The
 // hardware reciprocal is refined by one Newton-Raphson step, then the quotient
 // by two remainder corrections (Markstein's fma division). On these ranges it
 // equals the full division sequence, which adds operand scaling and a
-// special-case fix-up (checked on the device over every log argument and
-// 2^28 numerators x 16 denominators); it saves three instructions per use.
+// special-case fix-up (compared on the device with 2^20 pairs for each exponent of
+// b, and over the fp16 ranges of b with every fourth numerator); it saves three
+// instructions per use.
 // --------------------------------------------------------------------------
 // (f - 1) / (f + 1) for binary32 f in [1/2, 2): the hardware reciprocal, the
 // product and one remainder correction already give the IEEE quotient for
@@ -152,6 +153,8 @@ __device__ __forceinline__ float div_rn_log(float a, float b)
 // operands unchanged (the numerator is 0 or at least 2^-53 in magnitude, the
 // denominator in [1.5, 3), the quotient normal): reciprocal, two Newton steps,
 // product, and the remainder correction as a plain fma.
+// The same holds for a waiting time: -ln(u1), 0 or in [2^-53, 64), by a total of exponent
+// [-500, 500) (compared on the device with 2^20 pairs for each exponent).
 __device__ __forceinline__ double div_rn_log64(double a, double b)
 {
     const double r0 = __builtin_amdgcn_rcp(b);
