@@ -170,13 +170,14 @@ def copy_calib(log, nbytes=1 << 30):
 
 TRAFFIC_FILES = {"schlogl": "ssa_kernel_schlogl_100k_traffic.md",
                  "dimer_sweep": "ssa_kernel_dimer_sweep_traffic.md"}
+BUSY_FILES = {"dimer_sweep": "ssa_kernel_dimer_sweep_busy.md"}
 
 
-def measured_traffic(workload, mode, kernel_file):
-    """HBM bytes per step from the committed counter summary of the workload,
-    if it was taken on this exact kernel object (rows: | mode | object | ... |
-    bytes |)."""
-    name = TRAFFIC_FILES.get(workload)
+def measured(files, workload, mode, kernel_file):
+    """A figure of the committed counter summary of the workload (HBM bytes per
+    step, or the share of the step that the vector units are busy), if it was
+    taken on this exact kernel object (rows: | mode | object | ... | figure |)."""
+    name = files.get(workload)
     path = os.path.join(ROOT, "profiles", name) if name else None
     if not path or not os.path.exists(path):
         return None
@@ -199,6 +200,29 @@ def kernel_name(info):
     cus = torch.cuda.get_device_properties(torch.cuda.current_device()).multi_processor_count
     # (a grid of 512-thread workgroups counts four pipelined ones each)
     return "ssa_kernel_ph" if 4 * info["grid_size"] > cus else "ssa_kernel_pl"
+
+
+def one_wave_equivalent(res, counted):
+    """Events at the VALU slots of one in the one-wave event loop, whatever kernel ran them."""
+    rate = res["events_per_step"] * counted["valu_slots"] / (res["kernel_ms_avg"] * 1e-3)
+    return {"achieved": rate / 1e12, "unit": "TVALU-slot/s", "frac": rate / PEAK_VALU_SLOTS, "kernel": "ssa_kernel",
+            "valu_slots_per_event": counted["valu_slots"], "valu_insts_per_event": counted["valu_insts"]}
+
+
+def roofline(workload, mode, res, counted):
+    """The vector units' rate in the launched kernel: counted for the one-wave kernel,
+    measured (VALU-busy share of a step, null without counters of this object) for
+    the pipelined ones."""
+    kernel = kernel_name(res["info"])
+    if kernel == "ssa_kernel":
+        frac, source = one_wave_equivalent(res, counted)["frac"], "counted"
+    else:
+        frac = measured(BUSY_FILES, workload, mode, counted["file"])
+        source = "counters" if frac is not None else None
+    return {"bound": "alu", "achieved": None if frac is None else frac * PEAK_VALU_SLOTS / 1e12,
+            "peak": PEAK_VALU_SLOTS / 1e12, "unit": "TVALU-slot/s", "frac": frac, "source": source,
+            "traffic": measured(TRAFFIC_FILES, workload, mode, counted["file"]), "kernel": kernel,
+            "kernel_object": os.path.basename(counted["file"]), "kernel_ms": res["kernel_ms_avg"]}
 
 
 def physical_cores():
@@ -277,10 +301,12 @@ def main():
         fidelity["ks_pass_all"] = not fails
         fidelity["ks_fail"] = fails
 
-    # roofline: VALU slots of one event on the every-event path of the launched
-    # code object, counted on its one-wave event loop (ssa_kernel). In the pipelined
-    # kernels (ssa_kernel_pl, ssa_kernel_ph: 512-thread workgroups) the same per-event
-    # work is split between a workgroup's waves; the LDS traffic is not counted.
+    # VALU slots of one event on the every-event path of the code object's one-wave event
+    # loop (ssa_kernel). The pipelined kernels (ssa_kernel_pl, ssa_kernel_ph: 512-thread
+    # workgroups) divide an event between a workgroup's waves and execute other
+    # instructions (shorter draws; LDS traffic, and events past a trajectory's end), so
+    # events times these slots is work in the one-wave kernel's terms, not theirs: their
+    # share of the vector units comes from counters.
     # Several networks in one launch: the object's lightest loop would understate
     # the work, so each network's slots are counted on its own single-network
     # object and weighted by the events that network fired.
@@ -297,7 +323,6 @@ def main():
 
     ve, ve_ref = per_event(args.mode, main_res), per_event(args.ref_mode, ref_res)
     ms = main_res["kernel_ms_avg"]
-    achieved = main_res["events_per_step"] * ve["valu_slots"] / (ms * 1e-3)
     rate = main_res["events"] / main_res["wall_s"]
     # the metric counts events/s only where the ensemble passes KS against FP64
     passed = fidelity is not None and fidelity["ks_pass_all"]
@@ -328,9 +353,7 @@ def main():
                    "n_chunks": out_cfg_chunks},
         "fp64": {"value": ref_value, "unit": "events/s", "ms_per_step": ref_res["wall_s"] / args.steps * 1e3,
                  "kernel_ms": ref_res["kernel_ms_avg"], "events_per_step": ref_res["events_per_step"],
-                 "valu_slots_per_event": ve_ref["valu_slots"],
-                 "valu_frac": ref_res["events_per_step"] * ve_ref["valu_slots"] / (ref_res["kernel_ms_avg"] * 1e-3)
-                 / PEAK_VALU_SLOTS},
+                 "one_wave_equivalent": one_wave_equivalent(ref_res, ve_ref)},
         "speedup_vs_fp64": rate / ref_value,
         "fidelity": fidelity,
         "fidelity_gate": "passed" if passed else ("skipped" if fidelity is None else "failed"),
@@ -339,12 +362,8 @@ def main():
                                                      "placement")},
         "launch_fp64": {k: ref_res["info"][k] for k in ("block_size", "grid_size", "vgprs", "n_launches",
                                                           "first_window", "placement")},
-        "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_VALU_SLOTS / 1e12,
-                     "unit": "TVALU-slot/s", "frac": achieved / PEAK_VALU_SLOTS,
-                     "traffic": measured_traffic(W.name, args.mode, ve["file"]),
-                     "kernel": kernel_name(main_res["info"]),
-                     "kernel_object": os.path.basename(ve["file"]), "kernel_ms": ms,
-                     "valu_slots_per_event": ve["valu_slots"], "valu_insts_per_event": ve["valu_insts"]},
+        "roofline": roofline(W.name, args.mode, main_res, ve),
+        "one_wave_equivalent": one_wave_equivalent(main_res, ve),
     }
     # the chain bound: no launch ends before its longest trajectory has fired all
     # its events one after another; cycles per event of that chain at the nominal clock
