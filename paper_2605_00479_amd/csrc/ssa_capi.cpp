@@ -515,8 +515,17 @@ std::string gen_source(const std::vector<const Model *> &models, const ModeSpec 
     o << "#define SSA_N_ITEMS " << models.size() << "\n" << kDeviceSource << "\n";
     for (size_t i = 0; i < models.size(); ++i)
         o << gen_model(*models[i], (int)i, record_masks[i], ms.fmt);
+    int m_max = 0;
+    for (size_t i = 0; i < models.size(); ++i)
+        m_max = std::max(m_max, models[i]->M);
+    // Above 32 reactions the event loop would take more than 256 registers, for one wave a
+    // SIMD; held to two it spills some and is no slower for 1,024 waves and faster beyond
+    // (64 reactions, MIX_F16_SR, ms free and held: 6.3 and 5.9, 2,048 waves 12.1 and 9.6,
+    // 8,192 46.9 and 37.5). In FP64 the spills cost up to three times the time.
+    const bool two_waves = m_max > 32 && ms.fmt != SSA_FMT_FP64;
     o << "typedef " << ms.policy() << " PrecRun;\n"
-      << "extern \"C\" __global__ void __launch_bounds__(256) ssa_kernel(LaunchArgs L) {\n"
+      << "extern \"C\" __global__ void __launch_bounds__(256) "
+      << (two_waves ? "__attribute__((amdgpu_waves_per_eu(2))) " : "") << "ssa_kernel(LaunchArgs L) {\n"
       << "  const u32 wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;\n"
       << "  const u32 slot_rank = (threadIdx.x >> 6) * gridDim.x + blockIdx.x, n_slots = gridDim.x * (blockDim.x >> 6);\n"
       << "  u32 it = wave % SSA_N_ITEMS;\n"
@@ -530,9 +539,6 @@ std::string gen_source(const std::vector<const Model *> &models, const ModeSpec 
       << "    it = it + 1 == SSA_N_ITEMS ? 0 : it + 1;\n"
       << "  }\n"
       << "}\n";
-    int m_max = 0;
-    for (size_t i = 0; i < models.size(); ++i)
-        m_max = std::max(m_max, models[i]->M);
     // pipelined event loop: one workgroup to a CU (ssa_kernel_pl) and two (ssa_kernel_ph). Above
     // 16 reactions a wave has up to 256 registers and a SIMD two waves: one workgroup to a CU
     for (int half = 0; half < 2; ++half) {

@@ -62,6 +62,14 @@ def test_largest_network(gpu, orc, mode):
     one_wave(run, WORKGROUP)
 
 
+@pytest.mark.parametrize("mode", ["MIX_F16_SR", "UNI_BF16_SR"])
+def test_large_networks_keep_two_waves_a_simd(gpu, orc, mode):
+    run, _, _ = run_both(gpu, orc, largest_network(), np.full(32, 3, np.int32), 300, 1.0, [0.5, 1.0], mode, seed=2,
+                         **WORKGROUP)
+    one_wave(run, WORKGROUP)
+    assert run.info()["vgprs"] <= 256
+
+
 def test_the_default_for_a_large_ensemble_of_a_large_network(gpu, orc):
     # more workgroups of 64 trajectories than CUs, and 64 reactions
     n = 64 * 300
