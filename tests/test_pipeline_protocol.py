@@ -181,7 +181,7 @@ def clock_wave(sh, lanes, whole, queue, lengths, starts, ran):
                 e_done = sh.done_e
                 if signed(e_done - b) > 0:
                     break
-        restart = st["pending"] and (b == st["sw"] if whole else b & LOW == st["sw"] & LOW)
+        restart = st["pending"] and b & LOW == st["sw"] & LOW    # (pending: at most a ring ahead)
         if restart:
             act |= hold
             hold.clear()
