@@ -568,6 +568,7 @@ std::string gen_source(const std::vector<const Model *> &models, const ModeSpec 
           << "      if (lane < (u32)kPipeBatches) ctl.ready[lane] = 0u;\n"
           << "      ctl.done_e = 0u; ctl.done_c = 0u; ctl.done_s = 0u - 1024u; ctl.next = 0u; ctl.leave = 0u;\n"
           << "      ctl.gen = 0u; ctl.convw = 0u; ctl.sw[0] = 0u; ctl.sw[1] = 0u;\n"
+          << "      ctl.upper[0] = 0u; ctl.upper[1] = 0u;\n"
           << "    }\n"
           << "    __syncthreads();\n"
           << "    switch (L.item[turn].turn) {\n";

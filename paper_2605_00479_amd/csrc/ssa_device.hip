@@ -1203,7 +1203,10 @@ __device__ void run_item(const LaunchArgs &L, const ItemArgs &I, u32 slot_rank, 
 // `leave` ends all waits when the item has no trajectory left.
 // Batch numbers have 64 bits: a lane that runs one trajectory for 2^32 batches meets
 // the lower word of the last sw again. The counters carry lower words only, which is
-// enough to tell batches of one ring apart; a wave that needs the number counts on.
+// enough to tell batches of one ring apart. The draw and clock waves count the upper word;
+// the event wave, which needs it in its careful path only, finds it in upper[the lower
+// word's top bit], written by a draw wave 2^30 batches ahead (counted by the event wave in
+// every batch it cost the open dimer sweep 0.6% in MIX_F16_SR).
 // The tables of a lane are written while the other waves may read them (a draw wave
 // whose batch lies before sw, the event wave's careful path): such a lane holds no
 // trajectory in the batches that they work on, so nobody reads what they make of it,
@@ -1228,6 +1231,7 @@ struct __attribute__((aligned(16))) PipeCtl {
     u32 lanes[4 * kPipeBatches];   // clock to row wave: {lanes, restart} of a batch
     u32 done_e, done_c, done_s, next;
     u32 gen, convw, leave, sw[2];   // sw: lower and upper word
+    u32 upper[2];   // of the batches whose lower word begins with 0, with 1
     u32 rmask[2];   // lanes that start a trajectory at batch sw
     u32 live[2];    // lanes that hold one from batch sw on
 };
@@ -1607,6 +1611,8 @@ __device__ void pipe_draw(const LaunchArgs &L, const PipeWg &W)
             draws(PhiloxNear(any, (u32)(n0 >> 32)));
         else
             draws(any);
+        if (__builtin_expect((b & 0x7FFFFFFFu) == 0x40000000u, 0))   // the other half is 2^30 batches off
+            lds_st(&ctl->upper[(b >> 31) ^ 1u], (u32)(b64 >> 32) + (b >> 31));
         lds_fence();
         lds_st(ctl->ready + si, (b + 1u) << 2 | (b64 == sw ? 2u : 0u) | (conv ? 1u : 0u));
     }
@@ -1674,8 +1680,7 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
         return;
     u32 si_next = 0;
     __asm__ volatile(".p2align 6");
-    for (u64 b64 = 0;; ++b64) {
-        const u32 b = (u32)b64;
+    for (u32 b = 0;; ++b) {
         const u32 si = (u32)__builtin_amdgcn_readfirstlane(si_next);   // b mod nb
         u32 *slot = W.ring + si * G::SLOT;
         u32 first[FW];   // event 0's words, or every u2: in flight while the batch is looked over
@@ -1732,7 +1737,8 @@ __device__ void pipe_events(const LaunchArgs &L, const ItemArgs &I, const PipeWg
                     x[s] = x0[s];
                 mrun = m_start;
                 id = W.tab[G::T_ID + lane];
-                n = (((u64)W.tab[G::T_HI + lane] << 32) | W.tab[G::T_LO + lane]) + b64 * B;
+                n = (((u64)W.tab[G::T_HI + lane] << 32) | W.tab[G::T_LO + lane]) +
+                    (((u64)ctl_ld(&ctl->upper[b >> 31]) << 32) | b) * B;
 #pragma unroll
                 for (int k = 0; k < G::MUW; ++k)
                     muw[k] = 0u;

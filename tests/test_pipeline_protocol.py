@@ -47,6 +47,7 @@ class Shared:
         self.next = self.done_e = self.done_c = self.gen = self.leave = 0
         self.done_s = -64 & LOW       # nothing is drawn before the first claim
         self.sw = [0, 0]
+        self.upper = [0, 0]
         self.rmask = self.live = frozenset()
         self.t_id, self.t_off, self.t_x, self.t_k = ([None] * lanes for _ in range(4))
         self.draw = [[None] * lanes for _ in range(nb)]
@@ -84,6 +85,10 @@ def draw_wave(sh, lanes, whole):
             yield
             sh.draw[b64 % sh.nb][i] = (ids[i], None if offs[i] is None else offs[i] + b64 * B)
         yield
+        top = b >> (BITS - 1)
+        if b & (LOW >> 1) == 1 << (BITS - 2):
+            sh.upper[top ^ 1] = (b64 >> BITS) + top
+            yield
         mark = b64 == sw if whole else b == sw & LOW
         sh.ready[b64 % sh.nb] = ((b + 1) & TAG) << 1 | mark
         yield
@@ -131,7 +136,10 @@ def event_wave(sh, lanes, whole, rng, careful):
                 yield
                 off = sh.t_off[i]
                 yield
-                n = None if off is None else off + (b if whole else b & LOW) * B
+                low = b & LOW
+                upper = sh.upper[low >> (BITS - 1)] if whole else 0
+                yield
+                n = None if off is None else off + ((upper << BITS) + low) * B
                 out[i] = (out[i][0], (tid, n), b)
         for i in range(lanes):
             sh.result[slot][i] = out[i]
