@@ -353,6 +353,7 @@ def main():
                    "n_chunks": out_cfg_chunks},
         "fp64": {"value": ref_value, "unit": "events/s", "ms_per_step": ref_res["wall_s"] / args.steps * 1e3,
                  "kernel_ms": ref_res["kernel_ms_avg"], "events_per_step": ref_res["events_per_step"],
+                 "valu_busy": roofline(W.name, args.ref_mode, ref_res, ve_ref)["frac"],
                  "one_wave_equivalent": one_wave_equivalent(ref_res, ve_ref)},
         "speedup_vs_fp64": rate / ref_value,
         "fidelity": fidelity,
